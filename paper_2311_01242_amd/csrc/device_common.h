@@ -54,6 +54,9 @@ struct StateDesc {
     const double* ci_dgr;                // diagonal in occupation form: row part [na_str]
     const double* ci_dgc;                // column part (with the constant) [nb_str]
     const double* ci_dgx;                // alpha-beta pair coefficients [alpha][16]; null: none
+    const double* ci_g;                  // matrix form (k_hx_mm.hip): alpha move x beta move coefficients
+    const double* ci_ha;                 // same-spin matrices, padded to multiples of 16
+    const double* ci_hb;
     double2* aux;            // packed path: lambda in string-product order
     int32_t n, G, M, ne;
     uint32_t ref;            // basis index of the reference (full-vector layout)
@@ -205,6 +208,26 @@ struct CiArgs {
     // writes its partial lambda to aux plane z (na_str * nb_str entries each)
     int32_t nsplit;
     int32_t pad[2];
+};
+
+// The matrix form of the H-apply (k_hx_mm.hip) for one string space.
+constexpr uint32_t kMmNone = 1u << 30;
+constexpr int kMmChunks = 8;             // chunks of 16 beta moves (at most 13 orbitals: 91 moves)
+struct CiMmArgs {
+    const uint32_t* sa;      // alpha strings [na_str]
+    // the inputs of each row [na_str][kpad]: partner row, row of G << 16, bit
+    // 31 the parity of the occupied orbitals between the move's two, kMmNone
+    // for padding; the row's own occupations are input krow
+    const uint32_t* rows;
+    // per chunk, cnt[chunk] (a multiple of 4) entries of every column (entry-major [nb_str]):
+    // byte offset of the move's element of T, bit 0 the parity as above
+    const uint32_t* cols;
+    int32_t na_str, nb_str, na_pad, nb_pad;   // strings; padded to multiples of 16
+    int32_t krow, kpad;      // moves per row, na (oa - na); inputs with padding
+    int32_t ng;              // rows of G: alpha orbital pairs, orbital occupations, the rows' occupations
+    int32_t m_pad;           // beta moves, padded to a multiple of 16
+    int32_t t_stride;        // doubles per row of T
+    int32_t cnt[kMmChunks];
 };
 
 // A fused tile pass over consecutive excitation gates [g0, g1) that share
@@ -630,6 +653,9 @@ __device__ __forceinline__ void vadd(double2& a, double2 b) {
     a.y += b.y;
 }
 
+__device__ __forceinline__ double vneg(double a) { return -a; }
+__device__ __forceinline__ double2 vneg(double2 a) { return make_double2(-a.x, -a.y); }
+
 __device__ __forceinline__ double parity_sign(uint32_t v) {
     return (__popc(v) & 1) ? -1.0 : 1.0;
 }
@@ -682,8 +708,11 @@ void launch_hx_sector(const StateDesc* sd, int count, const HxPlan& plan, const 
 void launch_hx_packed(const StateDesc* sd, int count, const HxPlan& plan, const HxTables* tabs,
                       const int32_t* base, hipStream_t st);
 void launch_fill_zero(double2* p, uint64_t n, hipStream_t st);
+int mm_prepare(CiMmArgs* mm);   // sets kpad; 0 when the kernels can launch for these sizes
+void launch_hx_mm(const StateDesc* sd, int count, const CiMmArgs& mm, hipStream_t st);
 // Packed block order <-> string-product order: lam[perm[k]] = phi[k], and
-// lam[k] = aux[perm[k]].  real: the vectors hold doubles (real states).
+// lam[k] = aux[perm[k]], negated where perm's bit 31 is set.  real: the
+// vectors hold doubles (real states).
 void launch_ci_scatter(const StateDesc* sd, int count, const int32_t* perm, int64_t size, bool real,
                        hipStream_t st);
 void launch_ci_gather(const StateDesc* sd, int count, const int32_t* perm, int64_t size,

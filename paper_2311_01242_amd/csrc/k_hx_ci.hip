@@ -509,8 +509,11 @@ __global__ void k_ci_scatter(const StateDesc* __restrict__ sd, const int32_t* __
     const V* phi = reinterpret_cast<const V*>(s.phi);
     V* lam = reinterpret_cast<V*>(s.lam);
     for (int64_t k = blockIdx.x * int64_t(blockDim.x) + threadIdx.x; k < size;
-         k += int64_t(gridDim.x) * blockDim.x)
-        lam[perm[k]] = phi[k];
+         k += int64_t(gridDim.x) * blockDim.x) {
+        const int32_t q = perm[k];
+        const V v = phi[k];
+        lam[q & 0x7fffffff] = q < 0 ? vneg(v) : v;
+    }
 }
 
 // lambda in block order: the sum of the split planes, in plane order.
@@ -522,10 +525,11 @@ __global__ void k_ci_gather(const StateDesc* __restrict__ sd, const int32_t* __r
     V* lam = reinterpret_cast<V*>(s.lam);
     for (int64_t k = blockIdx.x * int64_t(blockDim.x) + threadIdx.x; k < size;
          k += int64_t(gridDim.x) * blockDim.x) {
-        const int64_t q = perm[k];
+        const int32_t p = perm[k];
+        const int64_t q = p & 0x7fffffff;
         V v = aux[q];
         for (int z = 1; z < nsplit; ++z) vadd(v, aux[size_t(z) * size + q]);
-        lam[k] = v;
+        lam[k] = p < 0 ? vneg(v) : v;
     }
 }
 

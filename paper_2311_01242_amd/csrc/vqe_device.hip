@@ -163,6 +163,13 @@ struct DiagParts {
     double* d_col = nullptr;
 };
 
+// Matrix form of a Hamiltonian on one string space (k_hx_mm.hip): one
+// allocation of G, Ha and Hb.
+struct CiMatrix {
+    double* d_all = nullptr;
+    const double *g = nullptr, *ha = nullptr, *hb = nullptr;
+};
+
 struct CiHam {
     std::vector<RowMoveGroup> rmg;
     std::map<const CiSpace*, RowMoves*> rm;        // by string space
@@ -190,6 +197,16 @@ struct CiHam {
     double2* pcoef = nullptr;   // pair coefficients by class, alpha pattern and pair
     int npcls = 0;
     bool psplit = false;   // pair records' beta sign masks split (see StateDesc::ci_psplit)
+    // host copies, uploaded when the walking kernel first needs them (ci_upload)
+    bool uploaded = false;
+    std::vector<CiChunk> chunks_h;
+    std::vector<CiGroup> groups_h, rgroups_h;
+    std::vector<CiSub> subs_h, rsubs_h;
+    std::vector<double> tabs_h, ptabs_h, hopa_h, dgx_h;
+    std::vector<CiPairClass> pcls_h;
+    std::vector<CiPairRec> precs_h;
+    std::vector<double2> pcoef_h;
+    std::map<const CiSpace*, CiMatrix*> mm;        // matrix form by string space (null: has none)
 };
 
 struct DevHam {
@@ -631,6 +648,7 @@ struct PackedLayout {
     std::vector<int32_t> base, bsize;    // per block h < 2^(n - L)
     int32_t* d_base = nullptr;
     int32_t* d_perm = nullptr;           // block order -> string-product order (or null)
+    int32_t* d_perm_s = nullptr;         // with the matrix form's amplitude sign in bit 31
 };
 
 // The run kernels' descriptor of tile o of run r (host side of the block
@@ -740,6 +758,9 @@ struct CiSpace {
     int16_t* d_rank_b = nullptr;
     int npairs = 0, e1 = 0;
     uint32_t* d_plist = nullptr;
+    bool mm_ok = false;              // the matrix form's kernels can launch
+    CiMmArgs mm{};
+    std::vector<int32_t> mm_pos;     // position of beta move R (pairs, then occupations) among T's rows
     CiArgs args() const {
         CiArgs a{};
         a.sa = d_sa;
@@ -762,6 +783,101 @@ static int pair_index(int p, int q, int ob) { return p * ob - p * (p + 1) / 2 + 
 
 constexpr int kCiMaxBits = 13;    // alpha / beta orbitals of the string-product path
 constexpr int kCiMaxCols = 1024;  // beta strings per row (16 per lane)
+
+// Tables of the matrix form of the H-apply for the strings of `c` (uploads
+// its row and column lists; mm_ok stays false where the kernels do not fit).
+static int mm_tables(CiSpace* c, int na, int nb) {
+    CiMmArgs& m = c->mm;
+    const int R = c->npairs + c->ob;
+    m.sa = c->d_sa;
+    m.na_str = c->NA;
+    m.nb_str = c->NB;
+    m.na_pad = (c->NA + 15) & ~15;
+    m.nb_pad = (c->NB + 15) & ~15;
+    const int pa = c->oa * (c->oa - 1) / 2;
+    m.ng = pa + c->oa + c->NA;
+    m.krow = na * (c->oa - na);
+    m.m_pad = (R + 15) & ~15;
+    m.t_stride = m.nb_pad;
+    const int nch = m.m_pad / 16;
+    if (c->NB < 1 || c->NB > 1024 || c->NA > 0xffff || m.ng > 0x3fff || R < 1 || nch > kMmChunks || mm_prepare(&m) != 0) return VQE_OK;
+    std::vector<uint32_t> rows(size_t(c->NA) * size_t(m.kpad));
+    for (int ia = 0; ia < c->NA; ++ia) {
+        const uint32_t a = c->sa[size_t(ia)];
+        uint32_t* row = &rows[size_t(ia) * size_t(m.kpad)];
+        int k = 0;
+        for (int p = 0; p < c->oa; ++p)
+            for (int q = p + 1; q < c->oa; ++q) {
+                if (((a >> p) & 1u) == ((a >> q) & 1u)) continue;
+                const uint32_t mid = a & ((1u << q) - 1u) & ~((2u << p) - 1u);
+                row[k++] = uint32_t(c->rank_a[a ^ (1u << p) ^ (1u << q)]) | (uint32_t(pair_index(p, q, c->oa)) << 16) |
+                           (uint32_t(__builtin_popcount(mid) & 1) << 31);
+            }
+        row[k++] = uint32_t(ia) | (uint32_t(pa + c->oa + ia) << 16);
+        for (; k < m.kpad; ++k) row[k] = uint32_t(ia) | kMmNone;
+    }
+    // the moves' order among T's rows: as they come, or dealt out over the
+    // chunks, whichever gives the shorter padded lists
+    struct Entry {
+        int R, col, par;
+    };
+    std::vector<std::vector<Entry>> per(static_cast<size_t>(c->NB));
+    for (int ib = 0; ib < c->NB; ++ib) {
+        const uint32_t b = c->sb[size_t(ib)];
+        for (int p = 0; p < c->ob; ++p)
+            for (int q = p + 1; q < c->ob; ++q) {
+                if (((b >> p) & 1u) == ((b >> q) & 1u)) continue;
+                const uint32_t mid = b & ((1u << q) - 1u) & ~((2u << p) - 1u);
+                per[size_t(ib)].push_back({pair_index(p, q, c->ob), c->rank_b[b ^ (1u << p) ^ (1u << q)],
+                                           __builtin_popcount(mid) & 1});
+            }
+        for (int u = 0; u < c->ob; ++u)
+            if ((b >> u) & 1u) per[size_t(ib)].push_back({c->npairs + u, ib, 0});
+    }
+    int best = 1 << 30;
+    for (int form = 0; form < 2; ++form) {
+        std::vector<int32_t> pos(static_cast<size_t>(R));
+        for (int r = 0; r < R; ++r) pos[size_t(r)] = form == 0 ? r : (r % nch) * 16 + r / nch;
+        int cnt[kMmChunks] = {}, sum = 0;
+        for (const auto& col : per) {
+            int here[kMmChunks] = {};
+            for (const Entry& e : col) ++here[pos[size_t(e.R)] / 16];
+            for (int k = 0; k < nch; ++k) cnt[k] = std::max(cnt[k], here[k]);
+        }
+        for (int k = 0; k < nch; ++k) {
+            cnt[k] = (cnt[k] + 3) & ~3;
+            sum += cnt[k];
+        }
+        if (sum >= best) continue;
+        best = sum;
+        c->mm_pos.swap(pos);
+        std::copy(cnt, cnt + kMmChunks, m.cnt);
+    }
+    std::vector<uint32_t> cols;
+    for (int k = 0; k < nch; ++k) {
+        const size_t at = cols.size();
+        cols.resize(at + size_t(m.cnt[k]) * c->NB, 16u * uint32_t(m.t_stride) * 8u);   // the zero
+        for (int ib = 0; ib < c->NB; ++ib) {
+            size_t e = 0;
+            for (const Entry& x : per[size_t(ib)]) {
+                const int r = c->mm_pos[size_t(x.R)];
+                if (r / 16 != k) continue;
+                cols[at + e++ * c->NB + size_t(ib)] = uint32_t((r % 16) * m.t_stride + x.col) * 8u | uint32_t(x.par);
+            }
+        }
+    }
+    uint32_t *d_rows = nullptr, *d_cols = nullptr;
+    int rc = upload(&d_rows, rows.data(), rows.size());
+    if (!rc) rc = upload(&d_cols, cols.data(), cols.size());
+    if (rc) {
+        (void)hipFree(d_rows);
+        return rc;
+    }
+    m.rows = d_rows;
+    m.cols = d_cols;
+    c->mm_ok = true;
+    return VQE_OK;
+}
 
 static std::mutex g_cis_mu;
 static std::map<std::tuple<int, int, int>, CiSpace*> g_cis;   // (dev, n, ne)
@@ -820,6 +936,7 @@ static int ci_space(int n, int ne, CiSpace** out) {
     if (!rc) rc = upload(&c->d_sb, c->sb.data(), c->sb.size());
     if (!rc) rc = upload(&c->d_rank_a, c->rank_a.data(), c->rank_a.size());
     if (!rc) rc = upload(&c->d_rank_b, c->rank_b.data(), c->rank_b.size());
+    if (!rc) rc = mm_tables(c, na, nb);
     if (rc) {
         (void)hipFree(c->d_sa);
         (void)hipFree(c->d_sb);
@@ -837,7 +954,7 @@ static int ci_space(int n, int ne, CiSpace** out) {
 // Block order -> string-product order of a packed layout.
 static int layout_perm(PackedLayout* lay, const CiSpace& cs, const HxTables& T) {
     if (lay->d_perm) return VQE_OK;
-    std::vector<int32_t> perm(size_t(lay->size));
+    std::vector<int32_t> perm(size_t(lay->size)), perm_s(size_t(lay->size));
     const uint32_t nblocks = uint32_t(lay->base.size());
     for (uint32_t h = 0; h < nblocks; ++h) {
         if (lay->bsize[h] == 0) continue;
@@ -850,9 +967,16 @@ static int layout_perm(PackedLayout* lay, const CiSpace& cs, const HxTables& T) 
             const int32_t ra = cs.rank_a[compact_even_host(b)];
             const int32_t rb = cs.rank_b[compact_even_host(b >> 1)];
             if (ra < 0 || rb < 0) return fail(VQE_EINVAL, "string-product order: string outside the sector");
+            // pairs of an occupied alpha and beta orbital, the alpha one later in the register
+            uint32_t cross = 0;
+            for (uint32_t m = b & 0xAAAAAAAAu; m; m &= m - 1)
+                cross ^= uint32_t(__builtin_popcount(b & 0x55555555u & ~((2u << __builtin_ctz(m)) - 1u)));
             perm[size_t(lay->base[h]) + k] = ra * cs.NB + rb;
+            perm_s[size_t(lay->base[h]) + k] = int32_t(uint32_t(ra * cs.NB + rb) | (cross << 31));
         }
     }
+    if (!lay->d_perm_s)
+        if (int rc = upload(&lay->d_perm_s, perm_s.data(), perm_s.size())) return rc;
     return upload(&lay->d_perm, perm.data(), perm.size());
 }
 
@@ -1342,38 +1466,227 @@ static int ci_ham(const vqe_hamiltonian* H, DevHam* d, CiHam** out) {
             }
     }
     c->diag = std::move(dform);
-    int rc = upload(&c->d_hopa, hopa.data(), hopa.size());
-    if (!rc && !dgx.empty()) rc = upload(&c->d_dgx, dgx.data(), dgx.size());
-    if (!rc) rc = upload(&c->chunks, chunks.data(), chunks.size());
-    if (!rc) rc = upload(&c->groups, grp.data(), grp.size());
-    if (!rc) rc = upload(&c->subs, sub.data(), sub.size());
-    if (!rc) rc = upload(&c->tabs, tab.data(), tab.size());
-    if (!rc) rc = upload(&c->pcls, pcls.data(), pcls.size());
-    if (!rc) rc = upload(&c->precs, precs.data(), precs.size());
-    if (!rc) rc = upload(&c->rgroups, rgrp.data(), rgrp.size());
-    if (!rc) rc = upload(&c->rsubs, rsub.data(), rsub.size());
-    if (!rc) rc = upload(&c->ptabs, ptab.data(), ptab.size());
-    if (!rc) rc = upload(&c->pcoef, pcoef.data(), pcoef.size());
-    if (rc) {
-        (void)hipFree(c->chunks);
-        (void)hipFree(c->groups);
-        (void)hipFree(c->subs);
-        (void)hipFree(c->tabs);
-        (void)hipFree(c->pcls);
-        (void)hipFree(c->precs);
-        (void)hipFree(c->rgroups);
-        (void)hipFree(c->rsubs);
-        (void)hipFree(c->ptabs);
-        (void)hipFree(c->pcoef);
-        (void)hipFree(c->d_hopa);
-        (void)hipFree(c->d_dgx);
-        delete c;
-        return rc;
-    }
+    c->hopa_h.swap(hopa);
+    c->dgx_h.swap(dgx);
+    c->chunks_h.swap(chunks);
+    c->groups_h.swap(grp);
+    c->subs_h.swap(sub);
+    c->tabs_h.swap(tab);
+    c->pcls_h.swap(pcls);
+    c->precs_h.swap(precs);
+    c->rgroups_h.swap(rgrp);
+    c->rsubs_h.swap(rsub);
+    c->ptabs_h.swap(ptab);
+    c->pcoef_h.swap(pcoef);
     d->ci = c;
     *out = c;
     return VQE_OK;
 }
+
+// Device copies of the walking kernel's plan.
+static int ci_upload(const vqe_hamiltonian* H, CiHam* c) {
+    std::lock_guard<std::mutex> lk(H->mu);
+    if (c->uploaded) return VQE_OK;
+    int rc = upload(&c->d_hopa, c->hopa_h.data(), c->hopa_h.size());
+    if (!rc) rc = upload(&c->d_dgx, c->dgx_h.data(), c->dgx_h.size());
+    if (!rc) rc = upload(&c->chunks, c->chunks_h.data(), c->chunks_h.size());
+    if (!rc) rc = upload(&c->groups, c->groups_h.data(), c->groups_h.size());
+    if (!rc) rc = upload(&c->subs, c->subs_h.data(), c->subs_h.size());
+    if (!rc) rc = upload(&c->tabs, c->tabs_h.data(), c->tabs_h.size());
+    if (!rc) rc = upload(&c->pcls, c->pcls_h.data(), c->pcls_h.size());
+    if (!rc) rc = upload(&c->precs, c->precs_h.data(), c->precs_h.size());
+    if (!rc) rc = upload(&c->rgroups, c->rgroups_h.data(), c->rgroups_h.size());
+    if (!rc) rc = upload(&c->rsubs, c->rsubs_h.data(), c->rsubs_h.size());
+    if (!rc) rc = upload(&c->ptabs, c->ptabs_h.data(), c->ptabs_h.size());
+    if (!rc) rc = upload(&c->pcoef, c->pcoef_h.data(), c->pcoef_h.size());
+    if (rc) {
+        for (void** p : {(void**)&c->chunks, (void**)&c->groups, (void**)&c->subs, (void**)&c->tabs, (void**)&c->pcls,
+                         (void**)&c->precs, (void**)&c->rgroups, (void**)&c->rsubs, (void**)&c->ptabs,
+                         (void**)&c->pcoef, (void**)&c->d_hopa, (void**)&c->d_dgx}) {
+            (void)hipFree(*p);
+            *p = nullptr;
+        }
+        return rc;
+    }
+    c->uploaded = true;
+    return VQE_OK;
+}
+
+// Matrix form of H on a string space (k_hx_mm.hip), from the families ci_ham
+// sorted its groups into, or null when H has none: a group outside the
+// families (other flips, or tables over other orbitals), a sign mask that is
+// not a Jordan-Wigner chain between the flipped orbitals, or a coefficient
+// that differs with the direction of a hop (more than rounding of the largest
+// coefficient) leaves H to the walking kernel.  Every Hamiltonian of real
+// two-body integrals with their 8-fold symmetry has one.
+static int ci_matrix(const vqe_hamiltonian* H, CiHam* c, const CiSpace& cs, const CiMatrix** out) {
+    std::lock_guard<std::mutex> lk(H->mu);
+    auto it = c->mm.find(&cs);
+    if (it != c->mm.end()) {
+        *out = it->second;
+        return VQE_OK;
+    }
+    *out = c->mm[&cs] = nullptr;
+    if (!cs.mm_ok || !c->diag.on || !c->psplit || !c->rgroups_h.empty() || !c->groups_h.empty()) return VQE_OK;
+    const int oa = cs.oa, ob = cs.ob, pa = oa * (oa - 1) / 2, n = H->n;
+    const int Mp = cs.mm.m_pad, NAp = cs.mm.na_pad, NBp = cs.mm.nb_pad;
+    double big = 0.0;
+    for (double v : H->tabs) big = std::max(big, std::fabs(v));
+    const double tol = 1e-14 * big;
+    auto par = [](uint32_t v) { return (__builtin_popcount(v) & 1) != 0; };
+    // beta orbitals whose occupation crosses an alpha flip mask x, and the reverse
+    auto cross_b = [&](uint32_t x) {
+        uint32_t m = 0;
+        for (int u = 0; u < ob; ++u)
+            if (par(x >> (u + 1))) m |= 1u << u;
+        return m;
+    };
+    auto cross_a = [&](uint32_t x) {
+        uint32_t m = 0;
+        for (int t = 0; t < oa; ++t)
+            if (par(x & ((1u << t) - 1u))) m |= 1u << t;
+        return m;
+    };
+    auto between = [](uint32_t x) {   // of a mask of two orbitals: those strictly between
+        const int p = __builtin_ctz(x), q = 31 - __builtin_clz(x);
+        return ((1u << q) - 1u) & ~((2u << p) - 1u);
+    };
+    auto bits_at = [](uint32_t x, int pat) {   // the pattern's bits (bit 0: lower orbital) at x's orbitals
+        return (pat & 1 ? 1u << __builtin_ctz(x) : 0u) | (pat & 2 ? 1u << (31 - __builtin_clz(x)) : 0u);
+    };
+    std::vector<double> all(size_t(cs.mm.ng) * Mp + size_t(NAp) * NAp + size_t(NBp) * NBp, 0.0);
+    double* G = all.data();
+    double* Ha = G + size_t(cs.mm.ng) * Mp;
+    double* Hb = Ha + size_t(NAp) * NAp;
+    // one coefficient from its values in every direction: equal up to rounding
+    auto agree = [&](const double* v, int k, double* mean) {
+        double lo = v[0], hi = v[0], sum = 0.0;
+        for (int i = 0; i < k; ++i) {
+            lo = std::min(lo, v[i]);
+            hi = std::max(hi, v[i]);
+            sum += v[i];
+        }
+        *mean = lo == hi ? lo : sum / k;
+        return hi - lo <= tol;
+    };
+    for (const CiPairClass& pc : c->pcls_h) {
+        if (__builtin_popcount(pc.xa) != 2 || pc.rest0 != pc.rest1) return VQE_OK;
+        const int P = pair_index(__builtin_ctz(pc.xa), 31 - __builtin_clz(pc.xa), oa);
+        for (int jp = 0; jp < cs.npairs; ++jp) {
+            const CiPairRec& r = c->precs_h[size_t(pc.rec0 + jp)];
+            if (r.tab < 0) continue;
+            const uint32_t xb = (1u << ((r.ka >> 8) & 0xff)) | (1u << ((r.ka >> 16) & 0xff));
+            const uint32_t N = cross_a(xb);
+            const uint32_t wa = r.wa ^ N ^ between(pc.xa), wb = r.wb ^ cross_b(pc.xa) ^ between(xb);
+            if ((r.ka & 0xff) != 2 || (wa & ~pc.xa) || (wb & ~xb)) return VQE_OK;
+            double v[4];
+            for (int e = 0; e < 4; ++e) {
+                const int ta = 1 + (e & 1), pat = 1 + (e >> 1);
+                const double t = c->ptabs_h[size_t(r.tab) + (ta | (pat << 2))];
+                const bool neg = par(pc.xa & N) ^ par(bits_at(pc.xa, ta) & wa) ^ par(bits_at(xb, pat) & wb);
+                v[e] = neg ? -t : t;
+            }
+            if (!agree(v, 4, &G[size_t(P) * Mp + cs.mm_pos[size_t(jp)]])) return VQE_OK;
+        }
+    }
+    auto add_ha = [&](int ia, int partner, double v) { Ha[size_t(ia) * NAp + partner] += v; };
+    auto add_hb = [&](int ib, int partner, double v) { Hb[size_t(partner) * NBp + ib] += v; };   // column ib: output
+    for (const AlphaHopGroup& g : c->ahg) {
+        const uint32_t odd = g.wa0 ^ between(g.xa);
+        if (g.wb0 != cross_b(g.xa) || (odd & ~g.xa)) return VQE_OK;
+        for (int u = 0; u < ob; ++u) {
+            double v[2];
+            for (int pat = 1; pat <= 2; ++pat)
+                v[pat - 1] = par(bits_at(g.xa, pat) & odd) ? -g.Tb[size_t(u) * 4 + pat] : g.Tb[size_t(u) * 4 + pat];
+            if (!agree(v, 2, &G[size_t(g.pair) * Mp + cs.mm_pos[size_t(cs.npairs + u)]])) return VQE_OK;
+        }
+        for (int ia = 0; ia < cs.NA; ++ia) {
+            const uint32_t a = cs.sa[size_t(ia)];
+            const int pat = int(((a >> g.lo) & 1u) | (((a >> g.hi) & 1u) << 1));
+            if (pat != 1 && pat != 2) continue;
+            double v = g.S[pat];
+            for (uint32_t m = a & ~g.xa; m; m &= m - 1) v += g.Ta[size_t(__builtin_ctz(m)) * 4 + size_t(pat)];
+            add_ha(ia, cs.rank_a[size_t(a ^ g.xa)], par(a & g.wa0) ? -v : v);
+        }
+    }
+    for (const BetaHopGroup& g : c->bhg) {
+        const uint32_t odd = g.wb0 ^ between(g.xb);
+        if (g.wa0 != cross_a(g.xb) || (odd & ~g.xb)) return VQE_OK;
+        for (int t = 0; t < oa; ++t) {
+            double v[2];
+            for (int pat = 1; pat <= 2; ++pat)
+                v[pat - 1] = par(bits_at(g.xb, pat) & odd) ? -g.Ta[size_t(t) * 4 + pat] : g.Ta[size_t(t) * 4 + pat];
+            if (!agree(v, 2, &G[size_t(pa + t) * Mp + cs.mm_pos[size_t(g.pair)]])) return VQE_OK;
+        }
+        for (int ib = 0; ib < cs.NB; ++ib) {
+            const uint32_t b = cs.sb[size_t(ib)];
+            const int pat = int(((b >> g.lo) & 1u) | (((b >> g.hi) & 1u) << 1));
+            if (pat != 1 && pat != 2) continue;
+            double v = g.S[pat];
+            for (uint32_t m = b & ~g.xb; m; m &= m - 1) v += g.Tb[size_t(__builtin_ctz(m)) * 4 + size_t(pat)];
+            add_hb(ib, cs.rank_b[size_t(b ^ g.xb)], par(b & g.wb0) ? -v : v);
+        }
+    }
+    auto pattern = [](uint32_t s, uint32_t tb) {   // s's bits at the table positions, ascending
+        uint32_t pat = 0;
+        int k = 0;
+        for (uint32_t m = tb; m; m &= m - 1, ++k) pat |= ((s >> __builtin_ctz(m)) & 1u) << k;
+        return size_t(pat);
+    };
+    for (const RowMoveGroup& g : c->rmg) {
+        if (g.wb != cross_b(g.xa)) return VQE_OK;
+        for (int ia = 0; ia < cs.NA; ++ia) {
+            const uint32_t a = cs.sa[size_t(ia)];
+            const int partner = cs.rank_a[size_t(a ^ g.xa)];
+            if (partner < 0) continue;
+            const double v = g.tab[pattern(a, g.tba)];
+            add_ha(ia, partner, par(a & g.wa) ? -v : v);
+        }
+    }
+    for (const ColMoveGroup& g : c->cmg) {
+        if (g.wa != cross_a(g.xb)) return VQE_OK;
+        for (int ib = 0; ib < cs.NB; ++ib) {
+            const uint32_t b = cs.sb[size_t(ib)];
+            const int partner = cs.rank_b[size_t(b ^ g.xb)];
+            if (partner < 0) continue;
+            const double v = g.tab[pattern(b, g.tbb)];
+            add_hb(ib, partner, par(b & g.wb) ? -v : v);
+        }
+    }
+    const DiagForm& d = c->diag;
+    auto part = [&](uint32_t s, int spin) {   // s: compact string of one spin
+        double v = 0.0;
+        for (uint32_t m = s; m; m &= m - 1) {
+            const int q = 2 * __builtin_ctz(m) + spin;
+            v += d.L[size_t(q)];
+            for (uint32_t m2 = m & (m - 1); m2; m2 &= m2 - 1)
+                v += d.Q[size_t(q) * n + 2 * __builtin_ctz(m2) + spin];
+        }
+        return v;
+    };
+    for (int ia = 0; ia < cs.NA; ++ia) add_ha(ia, ia, part(cs.sa[size_t(ia)], 0));
+    for (int ib = 0; ib < cs.NB; ++ib) add_hb(ib, ib, d.K + part(cs.sb[size_t(ib)], 1));
+    for (int t = 0; t < oa; ++t)
+        for (int u = 0; u < ob; ++u)
+            G[size_t(pa + t) * Mp + cs.mm_pos[size_t(cs.npairs + u)]] =
+                d.Q[size_t(std::min(2 * t, 2 * u + 1)) * n + std::max(2 * t, 2 * u + 1)];
+    for (int ia = 0; ia < cs.NA; ++ia)   // the occupations of each alpha string together
+        for (uint32_t o = cs.sa[size_t(ia)]; o; o &= o - 1)
+            for (int r = 0; r < Mp; ++r)
+                G[size_t(pa + oa + ia) * Mp + r] += G[size_t(pa + __builtin_ctz(o)) * Mp + r];
+    auto* m = new CiMatrix();
+    if (int rc = upload(&m->d_all, all.data(), all.size())) {
+        delete m;
+        c->mm.erase(&cs);
+        return rc;
+    }
+    m->g = m->d_all;
+    m->ha = m->g + size_t(cs.mm.ng) * Mp;
+    m->hb = m->ha + size_t(NAp) * NAp;
+    *out = c->mm[&cs] = m;
+    return VQE_OK;
+}
+
 
 // Smallest block-bit count for which every gate of A can run on the packed
 // layout (all excitations, annihilated orbitals in the low bits) and the
@@ -2067,6 +2380,7 @@ struct EvalPlan {
     const CiSpace* cspace = nullptr;
     CiArgs ciargs{};
     const int32_t* perm = nullptr;
+    bool mm = false;         // the matrix form of the H-apply (every Hamiltonian of the plan has one)
     bool real = false;       // packed path with real amplitudes (double, not double2)
     double pairs = 0.0;      // packed path: pair updates of one pass over the gates
     bool small = false;      // whole-state kernels on a small number-conserving sector
@@ -2253,7 +2567,10 @@ static void enqueue_packed(const EvalPlan& ep, const StateDesc* sd, int count, i
     } else if (phase == kPhaseHx) {
         if (ep.ci) {
             launch_ci_scatter(sd, count, ep.perm, ep.lay->size, ep.real, st);
-            launch_hx_ci(sd, count, ep.ciargs, ep.real, st);
+            if (ep.mm)
+                launch_hx_mm(sd, count, ep.cspace->mm, st);
+            else
+                launch_hx_ci(sd, count, ep.ciargs, ep.real, st);
             launch_ci_gather(sd, count, ep.perm, ep.lay->size, ep.ciargs.nsplit, ep.real, st);
         } else {
             launch_hx_packed(sd, count, ep.hx, ep.hxt, ep.lay->d_base, st);
@@ -2476,6 +2793,11 @@ vqe_hamiltonian::~vqe_hamiltonian() {
             (void)hipFree(c->rsubs);
             (void)hipFree(c->ptabs);
             (void)hipFree(c->pcoef);
+            for (auto& r : c->mm)
+                if (r.second) {
+                    (void)hipFree(r.second->d_all);
+                    delete r.second;
+                }
             for (auto& r : c->rm) {
                 (void)hipFree(r.second->d_rm);
                 (void)hipFree(r.second->d_off);
@@ -2735,6 +3057,84 @@ extern "C" int vqe_expectation(const vqe_state* s, const vqe_hamiltonian* H, dou
     return VQE_OK;
 }
 
+// Whether the matrix form of the H-apply serves H under plan ep: real
+// amplitudes, H has the form, and the sector has at least kMmMinSize strings.
+// Below that its second launch costs more than it saves: a 4-qubit energy and
+// gradient (4 strings) 99 us walking, 110 with it; 20 states of 12 qubits
+// (400 strings each) 170 us walking, 163 with it.
+constexpr int64_t kMmMinSize = 256;
+static int mm_choose(const vqe_hamiltonian* H, DevHam* dh, const EvalPlan& ep, bool* yes) {
+    *yes = false;
+    if (!ep.ci || !ep.real || ep.elems < kMmMinSize) return VQE_OK;
+    CiHam* ch;
+    if (int rc = ci_ham(H, dh, &ch)) return rc;
+    const CiMatrix* m;
+    if (int rc = ci_matrix(H, ch, *ep.cspace, &m)) return rc;
+    *yes = m != nullptr;
+    return VQE_OK;
+}
+static void mm_use(EvalPlan* ep) {
+    ep->mm = true;
+    ep->ciargs.nsplit = 1;
+    ep->perm = ep->lay->d_perm_s;
+    ep->nblk_e = ep->cspace->NA;
+}
+
+// A state's pointers to its Hamiltonian's string-product plan.
+static int ci_fill(const vqe_hamiltonian* H, DevHam* dh, const EvalPlan& ep, StateDesc* out) {
+    StateDesc& sd = *out;
+    CiHam* ch;
+    if (int rc = ci_ham(H, dh, &ch)) return rc;
+    if (ep.mm) {
+        const CiMatrix* m;
+        if (int rc = ci_matrix(H, ch, *ep.cspace, &m)) return rc;
+        sd.ci_g = m->g;
+        sd.ci_ha = m->ha;
+        sd.ci_hb = m->hb;
+        return VQE_OK;
+    }
+    if (int rc = ci_upload(H, ch)) return rc;
+    sd.ci_chunks = ch->chunks;
+    sd.ci_groups = ch->groups;
+    sd.ci_subs = ch->subs;
+    sd.ci_tabs = ch->tabs;
+    sd.ci_nchunks = ch->nchunks;
+    sd.ci_pcls = ch->pcls;
+    sd.ci_precs = ch->precs;
+    sd.ci_rgroups = ch->rgroups;
+    sd.ci_rsubs = ch->rsubs;
+    sd.ci_ptabs = ch->ptabs;
+    sd.ci_pcoef = ch->pcoef;
+    sd.ci_npcls = ch->npcls;
+    sd.ci_psplit = ch->psplit ? 1 : 0;
+    RowMoves* rm;
+    if (int rc = ci_rowmoves(H, ch, *ep.cspace, &rm)) return rc;
+    sd.ci_rm = rm->d_rm;
+    sd.ci_rm_off = rm->d_off;
+    ColMoves* cm;
+    if (int rc = ci_colmoves(H, ch, *ep.cspace, &cm)) return rc;
+    sd.ci_cm = cm->d_cm;
+    sd.ci_ncm = cm->ncm;
+    BetaHops* bh;
+    if (int rc = ci_betahops(H, ch, *ep.cspace, &bh)) return rc;
+    sd.ci_bh = bh->d_bh;
+    sd.ci_nbh = bh->nbh;
+    sd.ci_hopa = ch->d_hopa;
+    AlphaHops* ahp;
+    if (int rc = ci_alphahops(H, ch, *ep.cspace, &ahp)) return rc;
+    sd.ci_ah = ahp->d_ah;
+    sd.ci_ah_off = ahp->d_off;
+    sd.ci_ahb = ahp->d_b;
+    if (ch->diag.on) {
+        DiagParts* dp;
+        if (int rc = ci_diag(H, ch, *ep.cspace, &dp)) return rc;
+        sd.ci_dgr = dp->d_row;
+        sd.ci_dgc = dp->d_col;
+        sd.ci_dgx = ch->d_dgx;
+    }
+    return VQE_OK;
+}
+
 namespace {
 // Set-up of a single-state evaluation: plan, workspace, descriptor (uploaded
 // with theta); `extra` reserves more scratch for the caller.
@@ -2755,6 +3155,9 @@ int setup_single(const vqe_hamiltonian* H, const vqe_ansatz* A, int ne, const do
     if (int rc = dev_ham(H, &e->dh)) return rc;
     if (int rc = make_eval_plan(A, ne, false, &e->ep)) return rc;
     small_fit_ham(&e->ep, H);
+    bool mm;
+    if (int rc = mm_choose(H, e->dh, e->ep, &mm)) return rc;
+    if (mm) mm_use(&e->ep);
     if (int rc = dev_ansatz(A, &e->da)) return rc;
     const EvalPlan& ep = e->ep;
     HxWork* hw = nullptr;
@@ -2788,48 +3191,8 @@ int setup_single(const vqe_hamiltonian* H, const vqe_ansatz* A, int ne, const do
     sd.phi = ws->phi;
     sd.lam = ws->lam;
     sd.aux = ws->aux;
-    if (ep.ci) {
-        CiHam* ch;
-        if (int rc = ci_ham(H, e->dh, &ch)) return rc;
-        sd.ci_chunks = ch->chunks;
-        sd.ci_groups = ch->groups;
-        sd.ci_subs = ch->subs;
-        sd.ci_tabs = ch->tabs;
-        sd.ci_nchunks = ch->nchunks;
-        sd.ci_pcls = ch->pcls;
-        sd.ci_precs = ch->precs;
-        sd.ci_rgroups = ch->rgroups;
-        sd.ci_rsubs = ch->rsubs;
-        sd.ci_ptabs = ch->ptabs;
-        sd.ci_pcoef = ch->pcoef;
-        sd.ci_npcls = ch->npcls;
-        sd.ci_psplit = ch->psplit ? 1 : 0;
-        RowMoves* rm;
-        if (int rc = ci_rowmoves(H, ch, *ep.cspace, &rm)) return rc;
-        sd.ci_rm = rm->d_rm;
-        sd.ci_rm_off = rm->d_off;
-        ColMoves* cm;
-        if (int rc = ci_colmoves(H, ch, *ep.cspace, &cm)) return rc;
-        sd.ci_cm = cm->d_cm;
-        sd.ci_ncm = cm->ncm;
-        BetaHops* bh;
-        if (int rc = ci_betahops(H, ch, *ep.cspace, &bh)) return rc;
-        sd.ci_bh = bh->d_bh;
-        sd.ci_nbh = bh->nbh;
-        sd.ci_hopa = ch->d_hopa;
-        AlphaHops* ahp;
-        if (int rc = ci_alphahops(H, ch, *ep.cspace, &ahp)) return rc;
-        sd.ci_ah = ahp->d_ah;
-        sd.ci_ah_off = ahp->d_off;
-        sd.ci_ahb = ahp->d_b;
-        if (ch->diag.on) {
-            DiagParts* dp;
-            if (int rc = ci_diag(H, ch, *ep.cspace, &dp)) return rc;
-            sd.ci_dgr = dp->d_row;
-            sd.ci_dgc = dp->d_col;
-            sd.ci_dgx = ch->d_dgx;
-        }
-    }
+    if (ep.ci)
+        if (int rc = ci_fill(H, e->dh, ep, &sd)) return rc;
     Carver& cv = e->cv;
     sd.gates = e->da->gates;
     sd.theta = cv.take<double>(P);
@@ -3650,6 +4013,19 @@ extern "C" int vqe_batch_create(int S, const vqe_hamiltonian* const* H, const vq
             }
             persist = persist && b->classes[c].ep.packed && b->classes[c].ep.hx.L == Lp;
         }
+    {   // the matrix form of the H-apply for classes whose Hamiltonians all have one
+        std::vector<char> all(rep.size(), 1);
+        for (int i = 0; i < S; ++i) {
+            if (!all[size_t(cls[i])]) continue;
+            DevHam* dh;
+            if (int rc = dev_ham(H[i], &dh)) return rc;
+            bool yes;
+            if (int rc = mm_choose(H[i], dh, b->classes[cls[i]].ep, &yes)) return rc;
+            all[size_t(cls[i])] = yes;
+        }
+        for (size_t c = 0; c < rep.size(); ++c)
+            if (all[c]) mm_use(&b->classes[c].ep);
+    }
     size_t need = 0;
     for (int i = 0; i < S; ++i)
         need += (b->classes[cls[i]].ep.ci ? 3 : 2) * sizeof(double2) * size_t(b->classes[cls[i]].ep.elems);
@@ -3688,46 +4064,7 @@ extern "C" int vqe_batch_create(int S, const vqe_hamiltonian* const* H, const vq
         if (int rc = dalloc(b, &sd.lam, size_t(ep.elems))) return rc;
         if (ep.ci) {
             if (int rc = dalloc(b, &sd.aux, size_t(ep.elems))) return rc;
-            CiHam* ch;
-            if (int rc = ci_ham(H[i], dh, &ch)) return rc;
-            sd.ci_chunks = ch->chunks;
-            sd.ci_groups = ch->groups;
-            sd.ci_subs = ch->subs;
-            sd.ci_tabs = ch->tabs;
-            sd.ci_nchunks = ch->nchunks;
-            sd.ci_pcls = ch->pcls;
-            sd.ci_precs = ch->precs;
-            sd.ci_rgroups = ch->rgroups;
-            sd.ci_rsubs = ch->rsubs;
-            sd.ci_ptabs = ch->ptabs;
-            sd.ci_pcoef = ch->pcoef;
-            sd.ci_npcls = ch->npcls;
-            sd.ci_psplit = ch->psplit ? 1 : 0;
-            RowMoves* rm;
-            if (int rc = ci_rowmoves(H[i], ch, *ep.cspace, &rm)) return rc;
-            sd.ci_rm = rm->d_rm;
-            sd.ci_rm_off = rm->d_off;
-            ColMoves* cm;
-            if (int rc = ci_colmoves(H[i], ch, *ep.cspace, &cm)) return rc;
-            sd.ci_cm = cm->d_cm;
-            sd.ci_ncm = cm->ncm;
-            BetaHops* bh;
-            if (int rc = ci_betahops(H[i], ch, *ep.cspace, &bh)) return rc;
-            sd.ci_bh = bh->d_bh;
-            sd.ci_nbh = bh->nbh;
-            sd.ci_hopa = ch->d_hopa;
-            AlphaHops* ahp;
-            if (int rc = ci_alphahops(H[i], ch, *ep.cspace, &ahp)) return rc;
-            sd.ci_ah = ahp->d_ah;
-            sd.ci_ah_off = ahp->d_off;
-            sd.ci_ahb = ahp->d_b;
-            if (ch->diag.on) {
-                DiagParts* dp;
-                if (int rc = ci_diag(H[i], ch, *ep.cspace, &dp)) return rc;
-                sd.ci_dgr = dp->d_row;
-                sd.ci_dgc = dp->d_col;
-                sd.ci_dgx = ch->d_dgx;
-            }
+            if (int rc = ci_fill(H[i], dh, ep, &sd)) return rc;
         }
         launch_fill_zero(sd.lam, uint64_t(ep.elems), b->st);
         if (int rc = dalloc(b, &sd.cs, M)) return rc;
