@@ -65,6 +65,18 @@ static Tuning default_tuning(int n, bool batched) {
         // than the batch defaults there)
         L = std::min(n, 12);
         t.fwd_threads = t.adj_threads = 256;
+        // full-vector runs: tiles small enough to give a lone state many
+        // workgroups, whole states up to 10 qubits.  Measured, forward tiles of
+        // 512 / 1024 / 2048 / 4096 amplitudes: 16-qubit UCCSD state and its
+        // energy 328 / 342 / 392 / 515 us, 18 qubits 759 / 513 / 571 / 711, 19
+        // qubits 1288 / 797 / 854 / 1019, 20 qubits 2594 / 1999 / 1404 / 1546;
+        // 400 Pauli rotations on 14 qubits with their gradient, forward and
+        // reverse tiles of 512 962 us, of 4096 and 2048 1585
+        if (n <= 20) {
+            const int amps = n <= 10 ? 1024 : n <= 17 ? 512 : n <= 19 ? 1024 : 2048;
+            t.fwd_budget = int64_t(amps) * 16;
+            t.adj_budget = int64_t(amps) * 32;
+        }
     }
     t.L = L;
     return t;
