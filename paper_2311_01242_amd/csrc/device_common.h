@@ -694,6 +694,14 @@ void launch_adj_pauli(const StateDesc* sd, int count, int j, uint64_t N, int nbl
                       hipStream_t st);
 void launch_hx_dense(const StateDesc* sd, int count, uint64_t N, int nblk, int write_lam,
                      hipStream_t st);
+int dense_blocks(uint64_t N);   // energy partials of launch_hx_dense
+// Expectation value of phi: energy partials gx * gy (expect_grid).  With a
+// list (room for N indices, and nz_counts(N) counts) only the outputs at phi's
+// nonzero amplitudes are formed.
+void expect_grid(uint64_t N, int chunks, int* gx, int* gy);
+size_t nz_counts(uint64_t N);
+void launch_expect(const StateDesc* sd, const double2* phi, uint64_t N, int gx, int gy, uint32_t* cnt, uint32_t* list,
+                   hipStream_t st);
 void launch_reduce_e(const StateDesc* sd, int count, int nblk, hipStream_t st);
 void launch_param_grad(const int64_t* start, const int64_t* gate, const double* coef, const double* raw,
                        double* g, int64_t P, hipStream_t st);

@@ -302,6 +302,8 @@ static int dev_ham(const vqe_hamiltonian* H, DevHam** out) {
     return VQE_OK;
 }
 
+constexpr int kDenseL = 31;   // one batch of groups whatever their flips (the full-vector H-apply)
+
 // Work list of the sector H-apply for tile bits L: the groups (sorted by x,
 // hence by x >> L) cut into chunks that fit the kernel's LDS buffers.
 struct HxWork {
@@ -2532,7 +2534,7 @@ static int make_eval_plan(const vqe_ansatz* A, int ne, bool batched, EvalPlan* e
             }
         }
     } else {
-        ep->nblk_e = blocks_for(uint64_t(1) << n);
+        ep->nblk_e = dense_blocks(uint64_t(1) << n);
         // number-conserving programs on a small sector: whole-state kernels
         const uint32_t ref = A->ref_bits >= 0 ? uint32_t(A->ref_bits) : uint32_t((uint64_t(1) << ne) - 1);
         if (g_packed_enabled.load() >= 1 && n <= kSmallMaxN && number_conserving(A) &&
@@ -2935,7 +2937,7 @@ struct StateCall {
     StateDesc* sd_dev = nullptr;
 };
 
-int begin_state_call(const vqe_state* s, int64_t M, int64_t P, int nblk_e, StateCall* c) {
+int begin_state_call(const vqe_state* s, int64_t M, int64_t P, int nblk_e, StateCall* c, size_t words = 0) {
     ScratchSize sz;
     sz.add<double>(P);
     sz.add<double2>(M);
@@ -2943,6 +2945,7 @@ int begin_state_call(const vqe_state* s, int64_t M, int64_t P, int nblk_e, State
     sz.add<double>(nblk_e);
     sz.add<double>(1);
     sz.add<StateDesc>(1);
+    if (words) sz.add<uint32_t>(words);
     if (int rc = workspace(s->st, 0, 0, sz.s, &c->ws)) return rc;
     c->cv = Carver{c->ws->scratch};
     std::memset(&c->sd, 0, sizeof(StateDesc));
@@ -3050,18 +3053,23 @@ extern "C" int vqe_expectation(const vqe_state* s, const vqe_hamiltonian* H, dou
     DevHam* dh;
     if (int rc = dev_ham(H, &dh)) return rc;
     const uint64_t N = uint64_t(1) << s->n;
-    const int nblk = blocks_for(N);
+    HxWork* hw;
+    if (int rc = ham_chunks(H, dh, kDenseL, &hw)) return rc;
+    int gx, gy;
+    expect_grid(N, hw->count, &gx, &gy);
+    // the index list of the nonzero amplitudes, up to 64 MiB of it
+    const bool listed = s->n <= 24;
     StateCall c;
-    if (int rc = begin_state_call(s, 0, 0, nblk, &c)) return rc;
-    c.sd.groups = dh->groups;
-    c.sd.subs = dh->subs;
+    if (int rc = begin_state_call(s, 0, 0, gx * gy, &c, listed ? N + nz_counts(N) : 0)) return rc;
+    c.sd.chunks = hw->chunks;
+    c.sd.cgroups = hw->cgroups;
+    c.sd.csubs = hw->csubs;
+    c.sd.nb = hw->count;
     c.sd.tabs = dh->tabs;
-    c.sd.G = int32_t(H->groups.size());
-    c.sd.nsub = int32_t(H->subs.size());
-    c.sd.ntab = int32_t(H->tabs.size());
     HIPCHK(hipMemcpyAsync(c.sd_dev, &c.sd, sizeof(StateDesc), hipMemcpyHostToDevice, s->st));
-    launch_hx_dense(c.sd_dev, 1, N, nblk, 0, s->st);
-    launch_reduce_e(c.sd_dev, 1, nblk, s->st);
+    uint32_t* words = listed ? c.cv.take<uint32_t>(N + nz_counts(N)) : nullptr;
+    launch_expect(c.sd_dev, s->ptr, N, gx, gy, words, words ? words + nz_counts(N) : nullptr, s->st);
+    launch_reduce_e(c.sd_dev, 1, gx * gy, s->st);
     HIPCHK(hipGetLastError());
     HIPCHK(hipMemcpyAsync(energy, c.sd.out_e, sizeof(double), hipMemcpyDeviceToHost, s->st));
     HIPCHK(hipStreamSynchronize(s->st));
@@ -3173,8 +3181,8 @@ int setup_single(const vqe_hamiltonian* H, const vqe_ansatz* A, int ne, const do
     if (int rc = dev_ansatz(A, &e->da)) return rc;
     const EvalPlan& ep = e->ep;
     HxWork* hw = nullptr;
-    if (ep.sector)
-        if (int rc = ham_chunks(H, e->dh, ep.hx.L, &hw)) return rc;
+    if (!ep.small && !ep.ci)
+        if (int rc = ham_chunks(H, e->dh, ep.sector ? ep.hx.L : kDenseL, &hw)) return rc;
     ScratchSize sz = extra;
     sz.add<double>(P);
     sz.add<double2>(M);
@@ -4064,9 +4072,9 @@ extern "C" int vqe_batch_create(int S, const vqe_hamiltonian* const* H, const vq
         if (int rc = dev_ansatz(A[i], &da)) return rc;
         StateDesc& sd = sds[k];
         std::memset(&sd, 0, sizeof(sd));
-        if (ep.sector) {
+        if (!ep.small && !ep.ci) {
             HxWork* hw = nullptr;
-            if (int rc = ham_chunks(H[i], dh, ep.hx.L, &hw)) return rc;
+            if (int rc = ham_chunks(H[i], dh, ep.sector ? ep.hx.L : kDenseL, &hw)) return rc;
             sd.chunks = hw->chunks;
             sd.cgroups = hw->cgroups;
             sd.csubs = hw->csubs;
