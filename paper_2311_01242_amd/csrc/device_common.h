@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
+#include <utility>
 
 #include "internal.h"
 
@@ -442,6 +443,17 @@ struct HxPlan {
 
 // ---------------------------------------------------------------- helpers
 
+// Calls f(std::integral_constant<int, i>) for i = 0 .. N-1 in order (the
+// bodies see i as a constant).
+template <typename F, int... I>
+__device__ __forceinline__ void unroll_each(F&& f, std::integer_sequence<int, I...>) {
+    (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, typename F>
+__device__ __forceinline__ void unroll_n(F&& f) {
+    unroll_each(f, std::make_integer_sequence<int, N>{});
+}
+
 __device__ __forceinline__ double wave_sum(double v) {
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
@@ -753,6 +765,36 @@ int packed_shape_threads(int shape);
 int packed_enable_lds(size_t bytes);  // 0 on success
 
 int blocks_for(uint64_t work);
+
+// ------------------------------------------------- whole-state passes
+//
+// Sectors that fit one compute unit's LDS (k_whole.hip): amplitudes in
+// string-product order.  A pair's entry is two words, 8 times the indices of D
+// and E, swapped where the pair's sign is negative; threads without a pair have
+// two of the kWholeIdle dummies after the amplitudes.
+constexpr int kWholeMax = 10000;   // amplitudes: phi and lambda side by side in 160 KiB
+constexpr int kWholeIdle = 128;
+
+// Consecutive gates [g0, g1) of one kind: passes == 0, narrow (at most
+// `threads` pairs each), else wide (threads * passes).  ent: their first
+// entry.
+struct WholeSeg {
+    int32_t g0, g1, passes, ent;
+};
+
+struct WholeArgs {
+    const uint32_t* ent;     // two words per entry
+    const WholeSeg* seg;
+    int32_t nseg, nE, M;
+    int32_t threads;         // launch shape
+    int32_t ref, ref_neg;    // the reference's index; its amplitude is -1
+};
+
+int whole_prepare(int nE, int M, const int* cnt, int* threads);   // 0 when the kernels can launch
+// adj: also the energy (nblk_e partials) and the raw gradient sums; lambda is
+// the sum of nplanes planes of aux.
+void launch_whole(const StateDesc* sd, int count, const WholeArgs& w, bool adj, int nplanes, int nblk_e,
+                  hipStream_t st);
 
 // ------------------------------------------------------ small sectors
 //

@@ -21,22 +21,10 @@
 // high bits of the created orbitals only; generalised excitations may also
 // annihilate high orbitals.
 #include <type_traits>
-#include <utility>
 
 #include "device_common.h"
 
 namespace vqe {
-
-// Calls f(std::integral_constant<int, i>) for i = 0 .. N-1 in order (the
-// bodies see i as a constant).
-template <typename F, int... I>
-__device__ __forceinline__ void unroll_each(F&& f, std::integer_sequence<int, I...>) {
-    (f(std::integral_constant<int, I>{}), ...);
-}
-template <int N, typename F>
-__device__ __forceinline__ void unroll_n(F&& f) {
-    unroll_each(f, std::make_integer_sequence<int, N>{});
-}
 
 template <typename V>
 __global__ void k_packed_hf(const StateDesc* __restrict__ sd, int64_t size) {

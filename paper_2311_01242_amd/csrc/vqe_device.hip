@@ -257,7 +257,16 @@ struct PackedPlan {
     double pairs = 0.0;          // pair updates of one pass over the gates (live tiles)
 };
 
+// Whole-state plan of an ansatz on one string space (k_whole.hip).
+struct WholePlan {
+    WholeArgs args{};            // threads == 0: the state does not fit
+    uint32_t* d_ent = nullptr;
+    WholeSeg* d_seg = nullptr;
+    double pairs = 0.0;          // pair updates of one pass over the gates
+};
+
 struct DevAnsatz {
+    std::map<std::pair<const CiSpace*, int>, WholePlan*> whole;   // by string space and signed amplitudes
     GateDesc* gates = nullptr;
     std::map<std::pair<int64_t, int64_t>, AnsatzPlan*> plans;
     std::map<std::tuple<int, int, int, int>, PackedPlan*> packed;   // by (L, fwd, adj threads, tile cap)
@@ -1702,6 +1711,112 @@ static int ci_matrix(const vqe_hamiltonian* H, CiHam* c, const CiSpace& cs, cons
 }
 
 
+// Pairs of gate g (D in the sector: annihilated orbitals occupied, created ones
+// empty) as alpha pairs times beta pairs: appended are (D's row, E's row, sign)
+// and (D's column, E's column, sign); with `sgn` the signs include the matrix
+// form's amplitude signs of D and E.
+struct SpinPair {
+    int d, e, par;
+};
+static void whole_pairs(const GateDesc& g, const CiSpace& cs, bool sgn, std::vector<SpinPair>* rows,
+                        std::vector<SpinPair>* cols) {
+    const uint32_t xa = compact_even_host(g.x), xb = compact_even_host(g.x >> 1);
+    const uint32_t da = compact_even_host(g.pd), db = compact_even_host(g.pd >> 1);
+    const uint32_t ca = compact_even_host(g.chain), cb = compact_even_host(g.chain >> 1);
+    uint32_t Ma = 0, Mb = 0;   // amplitude signs: s(D) s(E) = (-1)^{|b_E & Mb| + |a_D & Ma|}
+    if (sgn) {
+        for (int u = 0; u < cs.ob; ++u)
+            if (__builtin_popcount(xa >> (u + 1)) & 1) Mb |= 1u << u;
+        for (int t = 0; t < cs.oa; ++t)
+            if (__builtin_popcount(xb & ((1u << t) - 1u)) & 1) Ma |= 1u << t;
+    }
+    rows->clear();
+    cols->clear();
+    for (int ia = 0; ia < cs.NA; ++ia) {
+        const uint32_t a = cs.sa[size_t(ia)];
+        if ((a & xa) != da) continue;
+        rows->push_back({ia, cs.rank_a[a ^ xa], (__builtin_popcount(a & ca) + __builtin_popcount(a & Ma)) & 1});
+    }
+    for (int ib = 0; ib < cs.NB; ++ib) {
+        const uint32_t b = cs.sb[size_t(ib)];
+        if ((b & xb) != db) continue;
+        cols->push_back({ib, cs.rank_b[b ^ xb], (__builtin_popcount(b & cb) + __builtin_popcount((b ^ xb) & Mb)) & 1});
+    }
+}
+
+static int whole_plan(const vqe_ansatz* A, DevAnsatz* da, const CiSpace& cs, uint32_t ref, bool sgn,
+                      const WholePlan** out) {
+    std::lock_guard<std::mutex> lk(A->mu);
+    const auto key = std::make_pair(&cs, sgn ? 1 : 0);
+    auto it = da->whole.find(key);
+    if (it != da->whole.end()) {
+        *out = it->second;
+        return VQE_OK;
+    }
+    const size_t M = A->gates.size();
+    std::vector<int> cnt(M);
+    std::vector<SpinPair> rows, cols;
+    for (size_t j = 0; j < M; ++j) {
+        whole_pairs(A->gates[j], cs, false, &rows, &cols);
+        cnt[j] = int(rows.size() * cols.size());
+    }
+    auto* p = new WholePlan();
+    for (int c : cnt) p->pairs += c;
+    WholeArgs& w = p->args;
+    w.nE = cs.NA * cs.NB;
+    w.M = int32_t(M);
+    int threads = 0;
+    if (whole_prepare(w.nE, w.M, cnt.data(), &threads) == 0) {
+        std::vector<uint32_t> ent;
+        std::vector<WholeSeg> seg;
+        for (size_t j = 0; j < M;) {
+            const bool wide = cnt[j] > threads;
+            size_t j2 = j;
+            int most = 0;
+            while (j2 < M && (cnt[j2] > threads) == wide) most = std::max(most, cnt[j2++]);
+            const int passes = wide ? (most + threads - 1) / threads : 1;
+            seg.push_back(WholeSeg{int32_t(j), int32_t(j2), wide ? passes : 0, int32_t(ent.size() / 2)});
+            for (; j < j2; ++j) {
+                whole_pairs(A->gates[j], cs, sgn, &rows, &cols);
+                const int neg = A->gates[j].csign < 0.0 ? 1 : 0;
+                for (const SpinPair& r : rows)
+                    for (const SpinPair& c : cols) {
+                        const uint32_t d = 8u * uint32_t(r.d * cs.NB + c.d), e = 8u * uint32_t(r.e * cs.NB + c.e);
+                        const bool swap = (r.par + c.par + neg) & 1;
+                        ent.push_back(swap ? e : d);
+                        ent.push_back(swap ? d : e);
+                    }
+                for (int k = cnt[j]; k < passes * threads; ++k) {   // a lane's own dummy pair
+                    const uint32_t idle = 8u * uint32_t(w.nE + 2 * (k & 63));
+                    ent.push_back(idle);
+                    ent.push_back(idle + 8u);
+                }
+            }
+        }
+        const uint32_t ra = compact_even_host(ref), rb = compact_even_host(ref >> 1);
+        w.ref = cs.rank_a[ra] * cs.NB + cs.rank_b[rb];
+        int cross = 0;   // alpha orbitals after a beta one
+        for (uint32_t m = rb; sgn && m; m &= m - 1)
+            cross += __builtin_popcount(ra & ~((2u << __builtin_ctz(m)) - 1u));
+        w.ref_neg = cross & 1;
+        int rc = upload(&p->d_ent, ent.data(), ent.size());
+        if (!rc) rc = upload(&p->d_seg, seg.data(), seg.size());
+        if (rc) {
+            (void)hipFree(p->d_ent);
+            (void)hipFree(p->d_seg);
+            delete p;
+            return rc;
+        }
+        w.ent = p->d_ent;
+        w.seg = p->d_seg;
+        w.nseg = int32_t(seg.size());
+        w.threads = threads;
+    }
+    da->whole[key] = p;
+    *out = p;
+    return VQE_OK;
+}
+
 // Smallest block-bit count for which every gate of A can run on the packed
 // layout (all excitations, annihilated orbitals in the low bits) and the
 // reference of ne electrons is entry 0 (block 0), or -1.
@@ -2394,6 +2509,7 @@ struct EvalPlan {
     const CiSpace* cspace = nullptr;
     CiArgs ciargs{};
     const int32_t* perm = nullptr;
+    const WholePlan* whole = nullptr;   // whole-state passes in string-product order (then lay and pp are null)
     bool mm = false;         // the matrix form of the H-apply (every Hamiltonian of the plan has one)
     bool real = false;       // packed path with real amplitudes (double, not double2)
     double pairs = 0.0;      // packed path: pair updates of one pass over the gates
@@ -2469,7 +2585,9 @@ static bool sector_path(const vqe_ansatz* A, int ne) {
 
 // force_L > 0: block bits of the packed layout (and sector H-apply tile)
 // regardless of the tuning (the persistent batch passes use one common value).
-static int make_eval_plan(const vqe_ansatz* A, int ne, bool batched, EvalPlan* ep, int force_L = 0) {
+// whole_ok: the caller can do without the block layout.
+static int make_eval_plan(const vqe_ansatz* A, int ne, bool batched, EvalPlan* ep, int force_L = 0,
+                          bool whole_ok = false) {
     const int n = A->n;
     ep->n = n;
     ep->ne = ne;
@@ -2500,6 +2618,37 @@ static int make_eval_plan(const vqe_ansatz* A, int ne, bool batched, EvalPlan* e
         ep->hx.nb = ne / 2;
         if (int rc = hx_tables(ep->hx.L, &ep->hxt)) return rc;
         ep->nblk_e = ep->hx.ntiles;
+        // a sector that fits one workgroup: whole-state passes (faster at every
+        // size measured, e.g. 16 qubits, one state: 203 us of both passes against
+        // 369 with tiled runs), unless a largest tile below it was asked for
+        if (ep->packed && whole_ok && g_packed_enabled.load() >= 2 && g_real_enabled.load() != 0 &&
+            (n + 1) / 2 <= kCiMaxBits) {
+            const int64_t size = binom((n + 1) / 2, (ne + 1) / 2) * binom(n / 2, ne / 2);
+            CiSpace* cs = nullptr;
+            if (size <= kWholeMax && (tn.tile_cap == 0 || tn.tile_cap >= size))
+                if (int rc = ci_space(n, ne, &cs)) return rc;
+            CiArgs args{};
+            if (cs && cs->NB <= kCiMaxCols) {
+                args = cs->args();
+                args.nsplit = batched ? 1 : ci_choose_splits(args);
+                if (int rc = whole_plan(A, da, *cs, uint32_t((uint64_t(1) << ne) - 1), false, &ep->whole)) return rc;
+                if (ep->whole->args.threads == 0 || ci_prepare(args) != 0) ep->whole = nullptr;
+            }
+            if (ep->whole) {
+                ep->ci = ep->real = true;
+                ep->cspace = cs;
+                ep->ciargs = args;
+                ep->nblk_e = cs->NA * args.nsplit;
+                ep->gstride = 1;
+                ep->d_gcnt = nullptr;
+                ep->elems = size;
+                ep->fwd_bytes = 8.0 * double(size);         // phi written
+                ep->adj_bytes = 2.0 * 8.0 * double(size);   // phi and lambda read
+                ep->pairs = ep->whole->pairs;
+                ep->fwd_steps = ep->adj_steps = 1;
+                return VQE_OK;
+            }
+        }
         if (ep->packed) {
             if (int rc = packed_layout(n, ne, ep->hx.L, &ep->lay)) return rc;
             if (int rc = packed_plan(A, da, *ep->lay, tn, &ep->pp)) return rc;
@@ -2570,6 +2719,21 @@ static int make_eval_plan(const vqe_ansatz* A, int ne, bool batched, EvalPlan* e
 enum Phase { kPhaseFwd = 0, kPhaseHx = 1, kPhaseAdj = 2, kPhaseReduce = 3 };
 
 // Enqueue one phase of an evaluation for `count` states at sd.
+static void enqueue_whole(const EvalPlan& ep, const StateDesc* sd, int count, int phase, bool grad,
+                          hipStream_t st) {
+    const WholeArgs& w = ep.whole->args;
+    if (phase == kPhaseFwd) {
+        launch_whole(sd, count, w, false, 1, 0, st);
+    } else if (phase == kPhaseHx) {
+        if (ep.mm) launch_hx_mm(sd, count, ep.cspace->mm, st);
+        else launch_hx_ci(sd, count, ep.ciargs, ep.real, st);
+    } else if (phase == kPhaseAdj) {
+        if (grad) launch_whole(sd, count, w, true, ep.ciargs.nsplit, ep.nblk_e, st);
+    } else if (!grad) {   // the reverse sweep writes the sums
+        launch_reduce_e(sd, count, ep.nblk_e, st);
+    }
+}
+
 static void enqueue_packed(const EvalPlan& ep, const StateDesc* sd, int count, int phase,
                            bool grad, hipStream_t st) {
     const PackedPlan& pp = *ep.pp;
@@ -2610,6 +2774,10 @@ static void enqueue_phase(const EvalPlan& ep, const StateDesc* sd, int count, in
             if (grad) launch_small(2, sd, count, ep.sspace, st);
         }
         // the H-apply writes the energy, the reverse sweep the per-gate sums
+        return;
+    }
+    if (ep.whole) {
+        enqueue_whole(ep, sd, count, phase, grad, st);
         return;
     }
     if (ep.packed) {
@@ -2858,6 +3026,11 @@ vqe_ansatz::~vqe_ansatz() {
             (void)hipFree(pl.second->d_gcnt);
             delete pl.second;
         }
+        for (auto& pl : kv.second->whole) {
+            (void)hipFree(pl.second->d_ent);
+            (void)hipFree(pl.second->d_seg);
+            delete pl.second;
+        }
         for (auto& pl : kv.second->packed) {
             (void)hipFree(pl.second->d_gates);
             (void)hipFree(pl.second->d_gcnt);
@@ -3093,11 +3266,17 @@ static int mm_choose(const vqe_hamiltonian* H, DevHam* dh, const EvalPlan& ep, b
     *yes = m != nullptr;
     return VQE_OK;
 }
-static void mm_use(EvalPlan* ep) {
+static int mm_use(EvalPlan* ep) {
     ep->mm = true;
     ep->ciargs.nsplit = 1;
-    ep->perm = ep->lay->d_perm_s;
     ep->nblk_e = ep->cspace->NA;
+    if (ep->whole) {   // the passes on signed amplitudes
+        DevAnsatz* da;
+        if (int rc = dev_ansatz(ep->A, &da)) return rc;
+        return whole_plan(ep->A, da, *ep->cspace, uint32_t((uint64_t(1) << ep->ne) - 1), true, &ep->whole);
+    }
+    ep->perm = ep->lay->d_perm_s;
+    return VQE_OK;
 }
 
 // A state's pointers to its Hamiltonian's string-product plan.
@@ -3169,15 +3348,16 @@ struct SingleEval {
 };
 
 int setup_single(const vqe_hamiltonian* H, const vqe_ansatz* A, int ne, const double* theta,
-                 hipStream_t st, const ScratchSize& extra, SingleEval* e) {
+                 hipStream_t st, const ScratchSize& extra, SingleEval* e, bool whole_ok = true) {
     const int n = H->n;
     const int64_t M = int64_t(A->gates.size()), P = A->n_params;
     if (int rc = dev_ham(H, &e->dh)) return rc;
-    if (int rc = make_eval_plan(A, ne, false, &e->ep)) return rc;
+    if (int rc = make_eval_plan(A, ne, false, &e->ep, 0, whole_ok)) return rc;
     small_fit_ham(&e->ep, H);
     bool mm;
     if (int rc = mm_choose(H, e->dh, e->ep, &mm)) return rc;
-    if (mm) mm_use(&e->ep);
+    if (mm)
+        if (int rc = mm_use(&e->ep)) return rc;
     if (int rc = dev_ansatz(A, &e->da)) return rc;
     const EvalPlan& ep = e->ep;
     HxWork* hw = nullptr;
@@ -3452,7 +3632,7 @@ int pool_gradient_impl(const vqe_hamiltonian* H, const vqe_ansatz* A, const vqe_
     extra.add<double>(Mp);                                       // pool raw sums
     extra.add<StateDesc>(1);
     SingleEval e;
-    if (int rc = setup_single(H, A, ne, theta, st, extra, &e)) return rc;
+    if (int rc = setup_single(H, A, ne, theta, st, extra, &e, false)) return rc;
     StateDesc sp = e.sd;   // the same phi, lambda; the pool's gates, angles and partials
     sp.gates = dp->gates;
     sp.theta = e.cv.take<double>(Pp);
@@ -4007,7 +4187,7 @@ extern "C" int vqe_batch_create(int S, const vqe_hamiltonian* const* H, const vq
     std::stable_sort(order.begin(), order.end(), [&](int a, int c) { return cls[a] < cls[c]; });
     b->classes.resize(rep.size());
     for (size_t c = 0; c < rep.size(); ++c)
-        if (int rc = make_eval_plan(A[rep[c]], ne[rep[c]], true, &b->classes[c].ep)) return rc;
+        if (int rc = make_eval_plan(A[rep[c]], ne[rep[c]], true, &b->classes[c].ep, 0, true)) return rc;
     // persistent gate passes: every class on the packed layout with one common
     // block-bit count (planned again with it), on a device whose XCDs the
     // probe identified
@@ -4044,7 +4224,8 @@ extern "C" int vqe_batch_create(int S, const vqe_hamiltonian* const* H, const vq
             all[size_t(cls[i])] = yes;
         }
         for (size_t c = 0; c < rep.size(); ++c)
-            if (all[c]) mm_use(&b->classes[c].ep);
+            if (all[c])
+                if (int rc = mm_use(&b->classes[c].ep)) return rc;
     }
     size_t need = 0;
     for (int i = 0; i < S; ++i)
