@@ -43,9 +43,10 @@ struct Tuning {
     int64_t fwd_budget;   // LDS bytes of a forward run tile
     int64_t adj_budget;   // LDS bytes of a reverse run tile (phi + lambda)
     int L;                // low-bit tile of the sector H-apply
-    int fwd_threads = 64; // packed layout: least threads per forward run tile
-    int adj_threads = 64; // packed layout: least threads per reverse run tile
-    int tile_cap = 0;     // packed layout: entries per run tile (0: two of the largest blocks)
+    int fwd_threads = 256; // packed layout: least threads per forward run tile
+    int adj_threads = 256; // packed layout: least threads per reverse run tile
+    int tile_cap = 0;      // packed layout: entries per run tile (0: two of the largest blocks)
+    int product_L = 0;     // packed layout before the string-product H-apply: block bits (0: L)
 };
 
 static std::mutex g_tune_mu;
@@ -60,11 +61,8 @@ static Tuning default_tuning(int n, bool batched) {
     int L = std::min(n, kHxMaxL);
     if (!batched) {
         // a single state: 12 block bits (the packed layout raises L to n_e when
-        // that is more) and 256-thread run tiles, measured best or within 1.5%
-        // of the best for single UCCSD states of 16 to 24 qubits (8-27% faster
-        // than the batch defaults there)
+        // that is more)
         L = std::min(n, 12);
-        t.fwd_threads = t.adj_threads = 256;
         // full-vector runs: tiles small enough to give a lone state many
         // workgroups, whole states up to 10 qubits.  Measured, forward tiles of
         // 512 / 1024 / 2048 / 4096 amplitudes: 16-qubit UCCSD state and its
@@ -79,6 +77,21 @@ static Tuning default_tuning(int n, bool batched) {
         }
     }
     t.L = L;
+    // Runs whose H-apply does not depend on L (string products): L down to
+    // half the qubits, so that a window of four high bits takes in more of a
+    // UCCSD program.  Real UCCSD states, forward + reverse, us: one state of 18
+    // qubits L = 9 / 10 / 12 281 / 296 / 359, 20 qubits L = 10 / 12 431 / 528, 22
+    // qubits L = 11 / 12 695 / 757; 55 x 18 qubits L = 9 / 10 / 11 565 / 496 / 540,
+    // 55 x 19 L = 10 / 11 900 / 910, 49 x 20 L = 10 / 11 / 12 1575 / 1507 / 1736, 16 x 22
+    // L = 11 / 12 2218 / 2513.  (24 qubits at half filling are at 12 anyway;
+    // with 8 electrons 11 costs a pool's sweep 10%.)
+    if (n >= 18 && n <= 22) t.product_L = std::min(11, n / 2 + (batched ? 1 : 0));
+    // Threads: a lone state's tiles leave most of the chip idle, so the steps'
+    // latency counts, a batch's the waves' overhead.  256 -> 512 threads: one
+    // state of 20 qubits 462 -> 431 us, 22 qubits 751 -> 695, but 24 qubits 1363
+    // -> 1400; 55 x 18 qubits 496 -> 631, 49 x 20 1507 -> 1819 (64 threads: 541 and
+    // 1574).
+    if (!batched && n >= 16 && n <= 22) t.fwd_threads = t.adj_threads = 512;
     return t;
 }
 
@@ -87,6 +100,7 @@ static Tuning tuning_for(int n, bool batched) {
     auto it = g_tune.find({n, batched ? 1 : 0});
     Tuning t = default_tuning(n, batched);   // an override replaces the budgets and L only
     if (it != g_tune.end()) {
+        t.product_L = 0;
         t.fwd_budget = it->second.fwd_budget;
         t.adj_budget = it->second.adj_budget;
         t.L = it->second.L;
@@ -242,7 +256,8 @@ struct PackedPlan {
     std::vector<int32_t> gcnt;        // gradient partials per gate (tiles of its run)
     int32_t* d_gcnt = nullptr;
     int32_t* d_gcnt_live = nullptr;   // the same for the reverse sweep (live tiles of its run)
-    int32_t gstride = 1;
+    int32_t gstride = 1;              // most tiles of a run
+    int32_t gstride_live = 1;         // most live tiles of a run
     size_t max_lds = 0;
     int max_entries = 0;              // largest tile (entries per vector)
     int max_stride = 0;               // longest padded pair list of a gate in a tile
@@ -2132,6 +2147,7 @@ static int packed_plan(const vqe_ansatz* A, DevAnsatz* da, const PackedLayout& l
             p->runs[r].live = listed ? p->d_live + live_of[r].first : nullptr;
             p->runs[r].nlive = listed ? int32_t(live_of[r].second) : p->runs[r].ntiles;
             p->runs[r].tdesc = p->d_tdesc + tdesc0[r];
+            p->gstride_live = std::max(p->gstride_live, p->runs[r].nlive);
             for (int k = p->runs[r].g0; k < p->runs[r].g1; ++k) gcnt_live[size_t(k)] = p->runs[r].nlive;
         }
     if (!rc) rc = upload(&p->d_gcnt_live, gcnt_live.data(), gcnt_live.size());
@@ -2608,9 +2624,18 @@ static int make_eval_plan(const vqe_ansatz* A, int ne, bool batched, EvalPlan* e
     ep->adj_steps = ep->ap->adj_steps.size();
     if (ep->sector) {
         ep->hx.L = std::min(n, tn.L);
+        // the string-product H-apply follows (the test below) and the sector is
+        // one of many tiles: the tuning's block bits for it (a sector of few
+        // tiles is fastest with few blocks: 30 complex states of 18 qubits and 4
+        // electrons L = 10 / 14 403 / 253 us)
+        int product_L = 0;
+        if (force_L == 0 && binom((n + 1) / 2, (ne + 1) / 2) * binom(n / 2, ne / 2) > kWholeMax && tn.product_L > 0 && g_packed_enabled.load() >= 2 && (n + 1) / 2 <= kCiMaxBits &&
+            binom(n / 2, ne / 2) <= kCiMaxCols)
+            product_L = tn.product_L;
         const int need = g_packed_enabled.load() ? packed_min_L(A, ne) : -1;
         if (need > 0 && need <= std::min(n, kHxMaxL)) {
             ep->packed = true;
+            if (product_L > 0) ep->hx.L = product_L;
             ep->hx.L = std::max(ep->hx.L, need);
         }
         ep->hx.ntiles = 1 << (n - ep->hx.L);
@@ -2652,7 +2677,9 @@ static int make_eval_plan(const vqe_ansatz* A, int ne, bool batched, EvalPlan* e
         if (ep->packed) {
             if (int rc = packed_layout(n, ne, ep->hx.L, &ep->lay)) return rc;
             if (int rc = packed_plan(A, da, *ep->lay, tn, &ep->pp)) return rc;
-            ep->gstride = ep->pp->gstride;
+            // the persistent passes (force_L) store a partial by tile, the runs
+            // by position in the live list
+            ep->gstride = force_L > 0 ? ep->pp->gstride : ep->pp->gstride_live;
             ep->d_gcnt = ep->pp->d_gcnt_live;
             ep->elems = ep->lay->size;
             ep->fwd_bytes = ep->pp->fwd_bytes;
