@@ -294,18 +294,6 @@ struct HxChunk {
     int32_t pad;
 };
 
-// A run on the packed sector layout: gates [g0, g1) whose created orbitals
-// have the same high part khi (bits of the block index h = b >> L).  Tile o
-// is the block pair (h, h | khi) with h = pdep(o, free_hi), or the single
-// block h when khi = 0.  shape selects the launch shape; max_entries bounds
-// the entries of one tile (LDS per vector).
-// Gate j of a run pairs, in a tile whose first block has electron class
-// cls = kA * (Lb + 1) + kB, the entries listed in ent[off, off + cnt) with
-// {off, cnt} = info[(j - g0) * ncls + cls]: D index (bits 0-10), E index in
-// the tile (bits 11-22), parity of the D string's low chain bits (bit 23).
-// Padding of a gate's pair list up to its class's stride.
-constexpr uint32_t kPairNone = 0xffffffffu;
-
 constexpr int kMaxTileBlocks = 16;   // blocks of one packed tile (window of at most 4 high bits)
 
 // A launched tile of a packed run, computed on the host: its entries, pair
@@ -316,11 +304,12 @@ struct TileDesc {
     int32_t nE;                       // entries (0: an empty tile)
     int32_t cls;                      // the pair lists' class
     uint32_t hbase;                   // high part of the tile's base (no window bits)
-    int32_t pad;
+    int32_t ent, stride, span;        // its pair lists, as the run's info has them
+    int32_t pad[2];
     int32_t off[kMaxTileBlocks];      // tile offset of each block (prefix sums)
     int32_t delta[kMaxTileBlocks];    // state offset minus tile offset of each block
 };
-static_assert(sizeof(TileDesc) == 144, "TileDesc is read as whole words");
+static_assert(sizeof(TileDesc) == 160, "TileDesc is read as whole words");
 
 // State-vector index of entry k (0 <= k < nE) of a tile.
 __device__ __forceinline__ int tile_index(const TileDesc& d, int nblk, int k) {
@@ -347,10 +336,14 @@ struct PackedRun {
     int32_t ntiles, L, na, nb;
     int32_t shape, shape_adj;     // launch shapes of the forward and reverse passes
     int32_t max_entries;          // largest tile (entries per vector)
+    uint32_t idle;                // the lists' padding
+    // bit t: waves must meet between the t-th gate of the pass and the next
+    // (where the bit is clear, every entry of the two is the same wave's)
+    uint64_t meet_fwd[kMaxRunGates / 64], meet_adj[kMaxRunGates / 64];
     int32_t ncls, cls_b;          // classes: a * cls_b + b, a/b the base's alpha/beta electrons
     int32_t nblk;                 // blocks per tile
     uint32_t blk[kMaxTileBlocks]; // their patterns within W
-    const int2* info;        // per class: {offset, stride} of the padded lists
+    const int2* info;        // per class: {offset, stride + 65536 (span / 64)} of the padded lists
     const uint32_t* ent;     // gate g of class c: ent[info[c].x + g * info[c].y + i]
     // the tiles that can hold a nonzero amplitude (starting from the
     // reference, a tile stays zero until a run pairs one of its blocks with a
@@ -367,12 +360,16 @@ struct PackedRun {
     const TileDesc* tdesc;
 };
 
-// Pair-list entry: D's index in the tile (bits 0-12), E's (bits 13-25), the
-// parity of D's chain bits in the low part and in the window (bit 26).
-constexpr int kEntBits = 13;
-constexpr uint32_t kEntMask = (1u << kEntBits) - 1u;
-constexpr int kEntParity = 2 * kEntBits;
-constexpr int kMaxTileEntries = 1 << kEntBits;
+// Pair-list entry: 8 times the pair's two indices in the tile, the first in
+// the low half: D and E, swapped where the parity of D's chain bits (those in
+// the low part and in the window) is odd, as a rotation by -s of (D, E) is one
+// by s of (E, D).  A gate's list is padded to its class's stride, a multiple of
+// 64, with the run's `idle`: the two entries after the largest tile.
+constexpr int kMaxTileEntries = (1 << 13) - 2;
+constexpr int kListAhead = 8;   // gates a list entry is loaded ahead, and read past a class's lists
+__host__ __device__ constexpr uint32_t pair_entry(int k, int ie) { return 8u * uint32_t(k) | (8u * uint32_t(ie)) << 16; }
+__device__ __forceinline__ int pair_first(uint32_t e) { return int((e & 0xffffu) >> 3); }
+__device__ __forceinline__ int pair_second(uint32_t e) { return int(e >> 19); }
 
 // The blocks of packed tile o of a run: base high part, the global offset and
 // tile offset of each block, total entries and class.  Uniform over a

@@ -44,15 +44,21 @@ __global__ void k_packed_hf(const StateDesc* __restrict__ sd, int64_t size) {
 // The tile's geometry is its host-built descriptor (one scalar read), so the
 // tile loads, the gate parameters and the first list entries are all in
 // flight together before the first wait.
+// What bounds it, one state of 20 qubits (a run of 46 gates, forward): 2.5 us of
+// loads before the first gate, then each wave's serial instruction stream.  A
+// gate took 436 cycles, 328 of them without its pair's work: address and clamp
+// arithmetic, two branches, a parity test; barriers and bank conflicts next to
+// nothing.  Hence a step of 20 instructions without a branch (an entry is two
+// LDS offsets, the sign their order, absent pairs a dummy), and, as the waits
+// that remain are then the barriers', waves that own whole groups of strings
+// (WaveSplit in vqe_device.hip) and meet once per stretch of gates.  Forward +
+// reverse, us: one state of 18 qubits 281 -> 243, 20 qubits 432 -> 356, 22 qubits 690 ->
+// 577, 24 qubits 1363 -> 1277; 49 states of 20 qubits, where LDS is busy half
+// of the time, 1507 -> 1481.
 template <int VEC, int BS, int EPT, typename V>
 __global__ void __launch_bounds__(BS) k_prun(const StateDesc* __restrict__ sd, PackedRun run,
                                              const PackedGate* __restrict__ pg) {
     extern __shared__ double2 sh[];
-    constexpr int kRedGates = 8;                            // gates per batch of wave totals
-    constexpr int kListAhead = 4;                           // list prefetch distance (gates)
-    static_assert(kRedGates % kListAhead == 0, "a batch of wave totals starts at slot 0");
-    __shared__ double red[2][VEC == 2 ? kRedGates : 1][BS / 64];   // wave totals of the last two batches
-    __shared__ double gsum[VEC == 2 ? kMaxRunGates : 1];   // per-gate tile totals
     const StateDesc& s = sd[blockIdx.y];
     // both passes cover the run's live tiles only (all of them without a list);
     // gradient partials go to the tile's position in the launch
@@ -67,46 +73,43 @@ __global__ void __launch_bounds__(BS) k_prun(const StateDesc* __restrict__ sd, P
     }
     const int nE = tb.nE;
     const uint32_t hb0 = tb.hbase << run.L;
+    const int nV = run.max_entries + 2;   // a vector: the tile and the lists' idle pair
     V* shp = reinterpret_cast<V*>(sh);
-    V* shl = shp + nE;
+    V* shl = shp + nV;
     // the reverse sweep on real amplitudes keeps (phi, lambda) of an entry
     // side by side, so that a pair's four values take two 16-byte LDS reads
     // and two writes
     constexpr bool kPL = VEC == 2 && std::is_same<V, double>::value;
     double2* shpl = sh;
-    const bool fwd = (VEC == 1);
+    constexpr bool fwd = VEC == 1;
     const int ng = run.g1 - run.g0;
-    const int cls = tb.cls;
-    // the tile class's pair lists: gate j's list at lbase + j * stride, padded
-    // with kPairNone.  Each thread's first entry of a gate is loaded kListAhead
-    // gates ahead (the first kListAhead before the tile loads) into slot
-    // t % kListAhead of eq; the gate loops are unrolled so that every slot
-    // index is a constant, so a gate waits only for its own entry's load and
-    // the list reads' latency overlaps kListAhead gate steps
-    const int2 lc = ldc(run.info + cls);
-    const uint32_t* lbase = run.ent + lc.x;
-    const int stride = lc.y;
-    // the loads go through a buffer resource bounded to the class's lists and
-    // are issued unconditionally for a clamped gate (reads past the lists
-    // return 0); a slot is checked only when its gate takes it (a thread past
-    // the list's length has no entry), so the compiler can wait for that
-    // slot's load alone while the later ones stay in flight
+    // the tile class's pair lists: gate j's list at lbase + j * stride.  Each
+    // thread's first entry of a gate is loaded kListAhead gates ahead (the
+    // first kListAhead before the tile loads) into slot t % kListAhead of eq;
+    // the gate loops are unrolled so that every slot index is a constant, so a
+    // gate waits only for its own entry's load and the list reads' latency
+    // overlaps kListAhead gate steps.  The loads run past both ends of the
+    // class's lists, unused (the lists' array has room for that): no clamp
+    const uint32_t* lbase = run.ent + tb.ent;
+    const int stride = tb.stride, span = tb.span;
+    const uint32_t rowb = uint32_t(stride) * 4u;
     const __amdgpu_buffer_rsrc_t lrs = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<uint32_t*>(lbase), 0, int(uint32_t(ng) * uint32_t(stride) * 4u), 0x00020000);
-    const bool has_slot = tid < stride;
-    auto list_first = [&](int j) -> uint32_t {   // raw: the thread's first entry of gate j
-        const int jc = j < 0 ? 0 : (j >= ng ? ng - 1 : j);
-        return __builtin_amdgcn_raw_buffer_load_b32(lrs, uint32_t(jc * stride + tid) * 4u, 0, 0);
-    };
+        const_cast<uint32_t*>(lbase - kListAhead * stride), 0, int(uint32_t(ng + 2 * kListAhead) * rowb), 0x00020000);
+    const bool has_slot = __builtin_amdgcn_readfirstlane(tid) < span;   // whole waves
+    const uint32_t voff = uint32_t(has_slot ? tid : 0) * 4u;
+    uint32_t row = uint32_t(kListAhead + (fwd ? 0 : ng - 1)) * rowb;   // of the next load
     uint32_t eq[kListAhead];
 #pragma unroll
-    for (int d = 0; d < kListAhead; ++d) eq[d] = list_first(fwd ? d : ng - 1 - d);
+    for (int d = 0; d < kListAhead; ++d) {
+        eq[d] = __builtin_amdgcn_raw_buffer_load_b32(lrs, voff, row, 0);
+        row += fwd ? rowb : 0u - rowb;
+    }
     // per-gate parameters of this tile after the tile (2 double2 per gate):
     // (cos, sgn sin) and (sgn, 0), sgn the gate's pair sign from the tile's
     // high bits outside the window (the window's part is in each entry);
     // staged once; the first is read by broadcast in the gate loop, the
     // second (reverse sweep) applied to the gate's tile total at the end
-    double2* gpar = sh + (size_t(VEC) * run.max_entries * sizeof(V) + 15) / 16;
+    double2* gpar = sh + (size_t(VEC) * nV * sizeof(V) + 15) / 16;
     // the state index of each staged entry, kept for the write-back
     int gix[2 * EPT];
     {   // all loads first (clamped into the tile), then the LDS stores
@@ -136,139 +139,137 @@ __global__ void __launch_bounds__(BS) k_prun(const StateDesc* __restrict__ sd, P
                 if (VEC == 2) shl[k] = vl[u];
             }
         }
+        if (tid < 2) {   // the idle pair
+            shp[(kPL ? 2 : 1) * (run.max_entries + tid)] = V{};
+            if (VEC == 2) (kPL ? shp + 1 : shl)[(kPL ? 2 : 1) * (run.max_entries + tid)] = V{};
+        }
     }
     __syncthreads();
-    // forward pass: the next gate's (cos, sgn sin) is read at the start of the
-    // current gate, so that only pair data follows the barrier (measured: the
-    // forward runs 4% faster, the reverse sweep, which reads the sign too, 5%
-    // slower, so it reads its parameters after the barrier)
-    double2 cs_ahead = gpar[0];
-    // one gate: its pairs (one per thread per pass), returning the thread's
-    // part of the reverse sweep's Re <lambda|A_j phi>; the slot's entry for
-    // gate t + kListAhead is loaded meanwhile.  LONG (a list longer than the
-    // block): the thread's later entries are read in the gate itself; the
-    // gate loops are built separately for the two cases, so that the common
-    // one has no other list reads than the slots'
-    auto gate_step = [&](int t, auto slot, auto long_tag) -> double {
-        constexpr int q = decltype(slot)::value;   // t % kListAhead
-        constexpr bool LONG = decltype(long_tag)::value;
-        const int jl = fwd ? t : ng - 1 - t;
-        const int jn = fwd ? jl + kListAhead : jl - kListAhead;
-        const uint32_t ecur = has_slot ? eq[q] : kPairNone;
-        const double2 cs = VEC == 1 ? cs_ahead : gpar[2 * jl];   // (cos, sgn sin)
-        const double ssin = cs.y;
-        if (VEC == 1) cs_ahead = gpar[2 * (jl + 1 < ng ? jl + 1 : jl)];
-        double acc = 0.0;
-        for (int i = tid; i < (LONG ? stride : tid + 1); i += BS) {
-            const uint32_t e = (i == tid) ? ecur : ldg32(lbase + size_t(jl) * stride + i);
-            if (e == kPairNone) break;   // the padding: the rest of the list is padding too
-            const int k = int(e & kEntMask), ie = int((e >> kEntBits) & kEntMask);
-            const double ss = ((e >> kEntParity) & 1u) ? -ssin : ssin;
-            if (fwd) {
-                V d = shp[k], f = shp[ie];
-                givens(d, f, cs.x, ss);
-                shp[k] = d;
-                shp[ie] = f;
+    // one pair; its part of the reverse sweep's Re <lambda|A_j phi>, A|D> =
+    // s|E>, A|E> = -s|D>, with the entry's part of s; the tile's, common to the
+    // gate, comes in when its total is stored
+    auto at = [&](V* v, uint32_t off) -> V& {
+        return *reinterpret_cast<V*>(reinterpret_cast<char*>(v) + off * uint32_t(sizeof(V) / 8));
+    };
+    auto pair = [&](uint32_t e, const double2& cs, double& acc) {
+        if constexpr (kPL) {
+            const uint32_t o0 = (e << 1) & 0x1fff0u, o1 = (e >> 15) & 0x1fff0u;
+            double2* q0 = reinterpret_cast<double2*>(reinterpret_cast<char*>(shpl) + o0);
+            double2* q1 = reinterpret_cast<double2*>(reinterpret_cast<char*>(shpl) + o1);
+            double2 d = *q0, f = *q1;
+            acc += d.x * f.y - d.y * f.x;
+            givens(d.x, f.x, cs.x, -cs.y);   // U^dag: rotation by -theta
+            givens(d.y, f.y, cs.x, -cs.y);
+            *q0 = d;
+            *q1 = f;
+        } else {
+            const uint32_t o0 = e & 0xffffu, o1 = e >> 16;
+            V d = at(shp, o0), f = at(shp, o1);
+            if constexpr (fwd) {
+                givens(d, f, cs.x, cs.y);
             } else {
-                V fD, fE, lD, lE;
-                if constexpr (kPL) {
-                    const double2 pD = shpl[k], pE = shpl[ie];
-                    fD = pD.x;
-                    lD = pD.y;
-                    fE = pE.x;
-                    lE = pE.y;
-                } else {
-                    fD = shp[k];
-                    fE = shp[ie];
-                    lD = shl[k];
-                    lE = shl[ie];
-                }
-                // <lam| A phi> with A|D> = s|E>, A|E> = -s|D> (s = ss / sin)
-                // the entry's part of the sign here; the tile's (a factor of
-                // +-1 common to the gate) when the tile's total is stored
-                const double dv = redot(lE, fD) - redot(lD, fE);
-                acc += ((e >> kEntParity) & 1u) ? -dv : dv;
-                givens(fD, fE, cs.x, -ss);   // U^dag: rotation by -theta
-                givens(lD, lE, cs.x, -ss);
-                if constexpr (kPL) {
-                    shpl[k] = make_double2(fD, lD);
-                    shpl[ie] = make_double2(fE, lE);
-                } else {
-                    shp[k] = fD;
-                    shp[ie] = fE;
-                    shl[k] = lD;
-                    shl[ie] = lE;
-                }
+                V lD = at(shl, o0), lE = at(shl, o1);
+                acc += redot(lE, d) - redot(lD, f);
+                givens(d, f, cs.x, -cs.y);
+                givens(lD, lE, cs.x, -cs.y);
+                at(shl, o0) = lD;
+                at(shl, o1) = lE;
+            }
+            at(shp, o0) = d;
+            at(shp, o1) = f;
+        }
+    };
+    // one gate: its pairs (one per thread per pass), returning the thread's
+    // part of the gate's total; the slot's entry for gate t + kListAhead is
+    // loaded meanwhile, and the next gate's (cos, sgn sin) read.  A place
+    // without a pair rotates the idle pair, so the step has no branch: what
+    // bounds it is the wave's serial instruction stream (about 16 per gate at 10 to
+    // 20 cycles each), not its LDS accesses or arithmetic.  LONG (a list
+    // longer than its span): the thread's later entries are read in the gate
+    // itself; the gate loops are built separately for the two cases, so that
+    // the common one has no other list reads than the slots'.  Between gates
+    // whose entries are the same waves' there is no barrier: a wave's LDS
+    // accesses are carried out in order, so it does not even wait for its
+    // writes.  Nothing moves across a gate's end: an address formed early would
+    // wait for its entry's load there
+    double2 cs_ahead = gpar[fwd ? 0 : 2 * (ng - 1)];
+    auto gate_step = [&](int jl, const double2* next, auto slot, auto long_tag, uint32_t meet) -> double {
+        constexpr int q = decltype(slot)::value;
+        constexpr bool LONG = decltype(long_tag)::value;
+        const double2 cs = cs_ahead;
+        cs_ahead = *next;
+        double acc = 0.0;
+        pair(eq[q], cs, acc);
+        if constexpr (LONG) {
+            for (int i = tid + span; i < stride; i += span) {
+                const uint32_t e = ldg32(lbase + size_t(jl) * stride + i);
+                if (uint32_t(__builtin_amdgcn_readfirstlane(int(e))) == run.idle) break;   // the wave's last
+                pair(e, cs, acc);
             }
         }
+        // (formed here: left to the round's end, where it is used, it would
+        // keep the pair's amplitudes in registers)
+        if constexpr (!fwd) __asm__ volatile("" : "+v"(acc));
         // the slot's next entry, issued once this gate's entry is dead (so
         // that it can take the same register)
-        eq[q] = list_first(jn);
-        __syncthreads();
+        eq[q] = __builtin_amdgcn_raw_buffer_load_b32(lrs, voff, row, 0);
+        row += fwd ? rowb : 0u - rowb;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_sched_barrier(0);
+        if (__builtin_expect((meet >> q) & 1u, 0)) __syncthreads();
+        __builtin_amdgcn_sched_barrier(0);
         return acc;
     };
-    // Whole rounds of slots (and whole batches of wave totals) run without
-    // per-gate bounds, so every one issues the same loads and a gate waits for
-    // its own slot only; the last, partial one checks each gate.
-    if (fwd) {
-        auto gates = [&](auto long_tag) {
-            int t0 = 0;
-            for (; t0 + kListAhead <= ng; t0 += kListAhead)
-                unroll_n<kListAhead>([&](auto slot) {
-                    (void)gate_step(t0 + decltype(slot)::value, slot, long_tag);
-                });
-            unroll_n<kListAhead>([&](auto slot) {
-                if (t0 + decltype(slot)::value < ng) (void)gate_step(t0 + decltype(slot)::value, slot, long_tag);
-            });
-        };
-        if (stride > BS) gates(std::true_type{});
-        else gates(std::false_type{});
-    } else {
-        // the wave totals of kRedGates consecutive gates are taken together
-        // after them (wave_totals8: off the per-gate barrier path); thread
-        // u < kRedGates adds the waves of gate u of the previous batch once a
-        // barrier has passed since they were written
-        static_assert(kRedGates == 8, "wave_totals8 takes eight gates");
-        auto batch = [&](int t0, auto long_tag, auto full_tag) {
-            constexpr bool FULL = decltype(full_tag)::value;
-            double acc[kRedGates];
-            unroll_n<kRedGates>([&](auto uu) {
-                constexpr int u = decltype(uu)::value;
-                acc[u] = 0.0;
-                if (FULL || t0 + u < ng) {
-                    acc[u] = gate_step(t0 + u, std::integral_constant<int, u % kListAhead>{}, long_tag);
-                    if (u == 0 && t0 > 0 && tid < kRedGates) {
-                        const int tp = t0 - kRedGates + tid;
-                        double v = 0.0;
-#pragma unroll
-                        for (int w = 0; w < BS / 64; ++w) v += red[(t0 / kRedGates - 1) & 1][tid][w];
-                        gsum[ng - 1 - tp] = v;
-                    }
-                }
-            });
+    // Whole rounds of slots run without per-gate bounds, so every one issues
+    // the same loads and a gate waits for its own slot only; the last, partial
+    // one checks each gate.  The reverse sweep takes the wave totals of a
+    // round's gates together after them (wave_totals8) into wsum; the waves
+    // are added after the last gate.
+    double* wsum = reinterpret_cast<double*>(gpar + 2 * ng);   // [ng][BS / 64], VEC = 2 only
+    auto meets = [&](int t0) -> uint32_t {   // of the gates t0 .. t0 + 7, t0 a multiple of 8
+        const uint64_t m = fwd ? (t0 < 64 ? run.meet_fwd[0] : run.meet_fwd[1])
+                               : (t0 < 64 ? run.meet_adj[0] : run.meet_adj[1]);
+        return uint32_t(m >> (t0 & 63)) & 0xffu;
+    };
+    auto round = [&](int t0, auto long_tag, auto full_tag) {
+        constexpr bool FULL = decltype(full_tag)::value;
+        const uint32_t meet = meets(t0);
+        const int j0 = fwd ? t0 : ng - 1 - t0;
+        double acc[kListAhead];
+        unroll_n<kListAhead>([&](auto uu) {
+            constexpr int u = decltype(uu)::value;
+            acc[u] = 0.0;
+            if (FULL || t0 + u < ng)   // (past the last gate: unused parameters)
+                acc[u] = gate_step(fwd ? j0 + u : j0 - u, gpar + 2 * j0 + (fwd ? 2 * (u + 1) : -2 * (u + 1)), uu,
+                                   long_tag, meet);
+        });
+        if constexpr (!fwd) {
+            static_assert(kListAhead == 8, "wave_totals8 takes eight gates");
             const double tot = wave_totals8(acc, tid & 63);
-            if ((tid & 7) == 0) red[(t0 / kRedGates) & 1][(tid & 63) >> 3][tid >> 6] = tot;
-        };
-        auto gates = [&](auto long_tag) {
-            int t0 = 0;
-            for (; t0 + kRedGates <= ng; t0 += kRedGates) batch(t0, long_tag, std::true_type{});
-            if (t0 < ng) batch(t0, long_tag, std::false_type{});
-        };
-        if (stride > BS) gates(std::true_type{});
-        else gates(std::false_type{});
-        __syncthreads();
-        {
-            const int t0 = (ng - 1) / kRedGates * kRedGates;   // the last batch
-            if (tid < kRedGates && t0 + tid < ng) {
-                double v = 0.0;
-#pragma unroll
-                for (int w = 0; w < BS / 64; ++w) v += red[(t0 / kRedGates) & 1][tid][w];
-                gsum[ng - 1 - (t0 + tid)] = v;
-            }
+            const int u = (tid & 63) >> 3;
+            if ((tid & 7) == 0 && (FULL || t0 + u < ng)) wsum[(j0 - u) * (BS / 64) + (tid >> 6)] = tot;
         }
-        __syncthreads();
-        for (int jl = tid; jl < ng; jl += BS)
-            s.part_g[size_t(run.g0 + jl) * s.gstride + po] = gsum[jl] * gpar[2 * jl + 1].x;
+    };
+    auto gates = [&](auto long_tag) {
+        int t0 = 0;
+        for (; t0 + kListAhead <= ng; t0 += kListAhead) round(t0, long_tag, std::true_type{});
+        if (t0 < ng) round(t0, long_tag, std::false_type{});
+    };
+    if (!has_slot) {   // a wave without pairs only meets the others
+        for (int t0 = 0; t0 < ng; t0 += 8)
+            for (int k = __builtin_popcount(meets(t0)); k > 0; --k) __syncthreads();
+    } else if (stride > span) {
+        gates(std::true_type{});
+    } else {
+        gates(std::false_type{});
+    }
+    __syncthreads();
+    if constexpr (!fwd) {
+        for (int jl = tid; jl < ng; jl += BS) {
+            double v = 0.0;
+            for (int w = 0; w < span / 64; ++w) v += wsum[jl * (BS / 64) + w];
+            s.part_g[size_t(run.g0 + jl) * s.gstride + po] = v * gpar[2 * jl + 1].x;
+        }
     }
 #pragma unroll
     for (int u = 0; u < 2 * EPT; ++u) {
@@ -346,18 +347,18 @@ __global__ void __launch_bounds__(BS) k_ppool(const StateDesc* __restrict__ sd,
     const int cls = tb.cls;
     const PackedGate* pg = pg_all + run.g0;
     const int2 lc = ldc(run.info + cls);
+    const int stride = lc.y & 0xffff;
     for (int jl = w; jl < ng; jl += BS / 64) {
-        const uint32_t* lst = run.ent + lc.x + size_t(jl) * lc.y;
+        const uint32_t* lst = run.ent + lc.x + size_t(jl) * stride;
         const PackedGate g = ldc(pg + jl);
         const double sgn_hi = g.csign * parity_sign(hb0 & g.chhi);
         double acc = 0.0;
-        for (int i = lane; i < lc.y; i += 64) {
+        for (int i = lane; i < stride; i += 64) {
             const uint32_t e = ldg32(lst + i);
-            if (e == kPairNone) break;
-            const int k = int(e & kEntMask), ie = int((e >> kEntBits) & kEntMask);
-            const double sg_t = ((e >> kEntParity) & 1u) ? -sgn_hi : sgn_hi;
+            if (e == run.idle) break;
+            const int k = pair_first(e), ie = pair_second(e);
             const V fD = shp[k], fE = shp[ie], lD = shl[k], lE = shl[ie];
-            acc += sg_t * (redot(lE, fD) - redot(lD, fE));
+            acc += sgn_hi * (redot(lE, fD) - redot(lD, fE));
         }
         acc = wave_total(acc);
         if (lane == 0) s.part_g[size_t(run.g0 + jl) * s.gstride + o] = acc;
@@ -395,9 +396,11 @@ using PackedLauncher = void (*)(const StateDesc*, int, const PackedRun&, const P
 template <int VEC, int BS, int EPT, typename V>
 static void launch_one(const StateDesc* sd, int count, const PackedRun& run, const PackedGate* pg,
                        hipStream_t st) {
-    // the tile's amplitudes (16-byte aligned), then 2 double2 per gate
-    const size_t lds = (size_t(run.max_entries) * VEC * sizeof(V) + 15) / 16 * 16 +
-                       2 * size_t(run.g1 - run.g0) * sizeof(double2);
+    // the tile's amplitudes and the idle pair (16-byte aligned), then 2 double2
+    // and the reverse sweep's wave totals per gate
+    const size_t lds = (size_t(run.max_entries + 2) * VEC * sizeof(V) + 15) / 16 * 16 +
+                       2 * size_t(run.g1 - run.g0) * sizeof(double2) +
+                       (VEC == 2 ? size_t(run.g1 - run.g0) * (BS / 64) * sizeof(double) : 0);
     const int nx = run.live ? run.nlive : run.ntiles;
     if (nx == 0) return;   // a run with no live tile: nothing to do, no partials
     hipLaunchKernelGGL((k_prun<VEC, BS, EPT, V>), dim3(nx, count), dim3(BS), lds, st, sd, run, pg);

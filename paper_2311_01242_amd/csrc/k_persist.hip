@@ -123,7 +123,7 @@ __device__ __forceinline__ void load_tile(const PqArgs& a, const HxTables& T, in
     d.empty = d.tb.nE == 0;
     const int2 lc = d.empty ? make_int2(0, 0) : ldc(d.run.info + d.tb.cls);
     d.lbase = d.run.ent + lc.x;
-    d.stride = lc.y;
+    d.stride = lc.y & 0xffff;
 }
 
 // Bounded wait until the item's state has `need` finished tiles; false when
@@ -205,11 +205,11 @@ __device__ __forceinline__ void apply_gate(const PqTile& d, int jl, const uint32
     double2 fD[PMAX], fE[PMAX], lD[PMAX], lE[PMAX];
     bool on[PMAX];
 #pragma unroll
-    for (int p = 0; p < PMAX; ++p) on[p] = (lane + 64 * p < d.stride) && e[p] != kPairNone;
+    for (int p = 0; p < PMAX; ++p) on[p] = (lane + 64 * p < d.stride) && e[p] != d.run.idle;
 #pragma unroll
     for (int p = 0; p < PMAX; ++p) {
         if (on[p]) {
-            const int k = int(e[p] & kEntMask), ie = int((e[p] >> kEntBits) & kEntMask);
+            const int k = pair_first(e[p]), ie = pair_second(e[p]);
             fD[p] = shp[k];
             fE[p] = shp[ie];
             if (VEC == 2) {
@@ -221,16 +221,13 @@ __device__ __forceinline__ void apply_gate(const PqTile& d, int jl, const uint32
 #pragma unroll
     for (int p = 0; p < PMAX; ++p) {
         if (on[p]) {
-            const int k = int(e[p] & kEntMask), ie = int((e[p] >> kEntBits) & kEntMask);
-            const bool neg = (e[p] >> kEntParity) & 1u;
-            const double ss = neg ? -cs.y : cs.y;
+            const int k = pair_first(e[p]), ie = pair_second(e[p]);
             if (fwd) {
-                givens(fD[p], fE[p], cs.x, ss);
+                givens(fD[p], fE[p], cs.x, cs.y);
             } else {
-                const double sg_t = neg ? -sgn_hi : sgn_hi;
-                acc += sg_t * ((lE[p].x * fD[p].x + lE[p].y * fD[p].y) - (lD[p].x * fE[p].x + lD[p].y * fE[p].y));
-                givens(fD[p], fE[p], cs.x, -ss);
-                givens(lD[p], lE[p], cs.x, -ss);
+                acc += sgn_hi * ((lE[p].x * fD[p].x + lE[p].y * fD[p].y) - (lD[p].x * fE[p].x + lD[p].y * fE[p].y));
+                givens(fD[p], fE[p], cs.x, -cs.y);
+                givens(lD[p], lE[p], cs.x, -cs.y);
                 shl[k] = lD[p];
                 shl[ie] = lE[p];
             }
@@ -240,19 +237,16 @@ __device__ __forceinline__ void apply_gate(const PqTile& d, int jl, const uint32
     }
     for (int i = lane + 64 * PMAX; OVF && i < d.stride; i += 64) {
         const uint32_t x = ldg32(d.lbase + size_t(jl) * d.stride + i);
-        if (x == kPairNone) break;
-        const int k = int(x & kEntMask), ie = int((x >> kEntBits) & kEntMask);
-        const bool neg = (x >> kEntParity) & 1u;
-        const double ss = neg ? -cs.y : cs.y;
+        if (x == d.run.idle) break;
+        const int k = pair_first(x), ie = pair_second(x);
         double2 dd = shp[k], ff = shp[ie];
         if (fwd) {
-            givens(dd, ff, cs.x, ss);
+            givens(dd, ff, cs.x, cs.y);
         } else {
             double2 ld = shl[k], le = shl[ie];
-            const double sg_t = neg ? -sgn_hi : sgn_hi;
-            acc += sg_t * ((le.x * dd.x + le.y * dd.y) - (ld.x * ff.x + ld.y * ff.y));
-            givens(dd, ff, cs.x, -ss);
-            givens(ld, le, cs.x, -ss);
+            acc += sgn_hi * ((le.x * dd.x + le.y * dd.y) - (ld.x * ff.x + ld.y * ff.y));
+            givens(dd, ff, cs.x, -cs.y);
+            givens(ld, le, cs.x, -cs.y);
             shl[k] = ld;
             shl[ie] = le;
         }

@@ -284,7 +284,7 @@ struct DevAnsatz {
     std::map<std::pair<const CiSpace*, int>, WholePlan*> whole;   // by string space and signed amplitudes
     GateDesc* gates = nullptr;
     std::map<std::pair<int64_t, int64_t>, AnsatzPlan*> plans;
-    std::map<std::tuple<int, int, int, int>, PackedPlan*> packed;   // by (L, fwd, adj threads, tile cap)
+    std::map<std::tuple<int, int, int, int, bool>, PackedPlan*> packed;   // by (L, fwd, adj threads, tile cap, ordered)
 };
 
 static int current_device(int* dev) {
@@ -292,12 +292,13 @@ static int current_device(int* dev) {
     return VQE_OK;
 }
 
+// front: elements of room before the copy.
 template <class T>
-static int upload(T** dst, const T* src, size_t count) {
+static int upload(T** dst, const T* src, size_t count, size_t front = 0) {
     *dst = nullptr;
     if (count == 0) return VQE_OK;
-    HIPCHK(hipMalloc(dst, count * sizeof(T)));
-    HIPCHK(hipMemcpy(*dst, src, count * sizeof(T), hipMemcpyHostToDevice));
+    HIPCHK(hipMalloc(dst, (front + count) * sizeof(T)));
+    HIPCHK(hipMemcpy(*dst + front, src, count * sizeof(T), hipMemcpyHostToDevice));
     return VQE_OK;
 }
 
@@ -692,7 +693,8 @@ struct PackedLayout {
 // The run kernels' descriptor of tile o of run r (host side of the block
 // geometry the pair lists were built with: block sizes from the popcount
 // tables, block starts from the layout's base offsets).
-static TileDesc host_tile_desc(const HxTables& T, const PackedRun& r, int o, const std::vector<int32_t>& base) {
+static TileDesc host_tile_desc(const HxTables& T, const PackedRun& r, int o, const std::vector<int32_t>& base,
+                               const int2* info) {
     TileDesc d{};
     uint32_t hb = 0, bits = r.free_hi, v = uint32_t(o);
     while (bits) {   // pdep(o, free_hi)
@@ -705,6 +707,9 @@ static TileDesc host_tile_desc(const HxTables& T, const PackedRun& r, int o, con
     const uint32_t hbg = hb << r.L;
     const int ca = __builtin_popcount(hbg & 0x55555555u), cb = __builtin_popcount(hbg & 0xAAAAAAAAu);
     d.cls = ca * r.cls_b + cb;
+    d.ent = info[d.cls].x;
+    d.stride = info[d.cls].y & 0xffff;
+    d.span = (info[d.cls].y >> 16) * 64;
     int acc = 0;
     for (int b = 0; b < kMaxTileBlocks; ++b) {
         d.off[b] = acc;
@@ -1832,6 +1837,164 @@ static int whole_plan(const vqe_ansatz* A, DevAnsatz* da, const CiSpace& cs, uin
     return VQE_OK;
 }
 
+// Division of consecutive gates' pairs (a | b << 16 each) among waves such that
+// no amplitude is touched by two waves.  The gates leave the bits outside their
+// orbitals as they are, so the strings with equal bits there form a group that
+// no gate leaves; the groups go to the waves, the largest first to the least
+// loaded one.
+// (A UCCSD stretch that creates the same orbitals never joins strings that
+// differ in the other virtual ones.)  A single gate's pairs are divided in
+// order.
+struct WaveSplit {
+    // The amplitudes in order: per block the products of alpha and beta strings
+    // (compact, of the low `bits` orbitals of each spin), hi its other bits.
+    struct Block {
+        uint32_t hi;
+        const uint16_t *a, *b;
+        int na, nb;
+    };
+    std::vector<Block> blocks;     // set by the caller
+    int low = 0;                   // qubits below hi
+    std::vector<uint16_t> label;   // by amplitude: its group
+    std::vector<uint32_t> load;    // by group
+    std::vector<uint16_t> order;
+    std::vector<uint8_t> wave;     // by group
+    std::vector<uint16_t> ida, idb;   // string without the gates' orbitals -> number
+
+    bool one = false;   // the division is in order
+    int nw = 1;
+    // Sets the division of gates [0, n).
+    void set(const GateDesc* gates, const std::vector<uint32_t>* lists, size_t n, int waves) {
+        nw = waves;
+        one = n == 1;
+        if (one || nw == 1) return;
+        uint32_t U = 0;
+        for (size_t k = 0; k < n; ++k) U |= gates[k].x;
+        const uint32_t lowmask = (1u << low) - 1u, hi_keep = ~U & ~lowmask;
+        const uint32_t keep_a = compact_even_host(~U & lowmask), keep_b = compact_even_host((~U & lowmask) >> 1);
+        ida.assign(size_t(1) << ((low + 1) / 2), 0xffffu);
+        idb.assign(size_t(1) << ((low + 1) / 2), 0xffffu);
+        uint32_t na = 0, nb = 0, his[kMaxTileBlocks], nhi = 0, entries = 0;
+        for (const Block& x : blocks) {
+            for (int i = 0; i < x.na; ++i)
+                if (ida[x.a[i] & keep_a] == 0xffffu) ida[x.a[i] & keep_a] = uint16_t(na++);
+            for (int i = 0; i < x.nb; ++i)
+                if (idb[x.b[i] & keep_b] == 0xffffu) idb[x.b[i] & keep_b] = uint16_t(nb++);
+            entries += uint32_t(x.na) * uint32_t(x.nb);
+        }
+        label.resize(entries);
+        uint16_t* l = label.data();
+        for (const Block& x : blocks) {
+            uint32_t h = 0;
+            while (h < nhi && his[h] != (x.hi & hi_keep)) ++h;
+            if (h == nhi) his[nhi++] = x.hi & hi_keep;
+            for (int i = 0; i < x.na; ++i) {
+                const uint32_t row = (h * na + ida[x.a[i] & keep_a]) * nb;
+                for (int k = 0; k < x.nb; ++k) *l++ = uint16_t(row + idb[x.b[k] & keep_b]);
+            }
+        }
+        const uint32_t groups = nhi * na * nb;   // (from 2^16 on groups share labels, still a division)
+        load.assign(groups, 0);
+        for (size_t k = 0; k < n; k += n > 8 ? 2 : 1)   // (a sample will do)
+            for (uint32_t e : lists[k]) ++load[label[e & 0xffffu]];
+        wave.resize(groups);
+        uint32_t sum[16] = {};
+        if (groups <= 64) {
+            order.resize(groups);
+            for (uint32_t g = 0; g < groups; ++g) order[g] = uint16_t(g);
+            std::stable_sort(order.begin(), order.end(), [&](uint16_t x, uint16_t y) { return load[x] > load[y]; });
+            for (uint16_t g : order) {
+                const int w = int(std::min_element(sum, sum + nw) - sum);
+                wave[g] = uint8_t(w);
+                sum[w] += load[g];
+            }
+        } else {   // many small groups: dealt out by load, to and fro
+            uint32_t at[65] = {};
+            for (uint32_t g = 0; g < groups; ++g) ++at[std::min<uint32_t>(load[g], 63)];
+            for (uint32_t k = 64, before = 0; k-- > 0;) {   // the largest loads first
+                const uint32_t c = at[k];
+                at[k] = before;
+                before += c;
+            }
+            for (uint32_t g = 0; g < groups; ++g) {
+                const uint32_t i = at[std::min<uint32_t>(load[g], 63)]++, t = i % (2 * uint32_t(nw));
+                wave[g] = uint8_t(t < uint32_t(nw) ? t : 2 * uint32_t(nw) - 1 - t);
+            }
+        }
+    }
+    uint32_t of(uint32_t e, size_t i) const {   // the i-th pair of its gate
+        return nw == 1 ? 0u : one ? uint32_t(i / 64) % uint32_t(nw) : wave[label[e & 0xffffu]];
+    }
+    // Pairs of each wave.
+    void count(const std::vector<uint32_t>& list, uint32_t (&c)[16]) const {
+        for (uint32_t& x : c) x = 0;
+        if (one || nw == 1) {
+            const size_t n = list.size(), rows = n / (64 * size_t(nw)), rest = n - rows * 64 * size_t(nw);
+            for (int w = 0; w < nw; ++w)
+                c[w] = uint32_t(rows * 64 + std::min<size_t>(64, rest > size_t(w) * 64 ? rest - size_t(w) * 64 : 0));
+        } else {
+            for (uint32_t e : list) ++c[wave[label[e & 0xffffu]]];
+        }
+    }
+    // Most passes of 64 pairs of a wave over the gates.
+    uint32_t passes(const GateDesc* gates, const std::vector<uint32_t>* lists, size_t n, int waves) {
+        set(gates, lists, n, waves);
+        uint32_t most[16] = {}, c[16];
+        for (size_t k = 0; k < n; ++k) {
+            count(lists[k], c);
+            for (int w = 0; w < nw; ++w) most[w] += (c[w] + 63) / 64;
+        }
+        return *std::max_element(most, most + nw);
+    }
+    // A gate's list with a place of 64 entries per wave and pass.
+    void place(const std::vector<uint32_t>& list, uint32_t* out) const {
+        uint32_t c[16] = {};
+        for (size_t i = 0; i < list.size(); ++i) {
+            const uint32_t w = of(list[i], i), k = c[w]++;
+            out[((k >> 6) * uint32_t(nw) + w) * 64 + (k & 63u)] = list[i] << 3;
+        }
+    }
+};
+
+// Where the waves must meet: cut[k] set where gate k + 1 starts a new division.
+// Candidates for each stretch of gates with the same created orbitals are one
+// division, one per stretch that also shares an annihilated orbital, and one
+// per gate; a meeting is taken as 1.5 passes of 64 pairs.  Against a meeting after
+// every gate (forward + reverse, us): one state of 20 qubits 592 -> 518, 55 x 18
+// qubits 674 -> 636, 49 x 20 qubits 2329 -> 2183 (on an early form of the reverse
+// sweep that spilled registers).
+static void wave_cuts(const GateDesc* gates, size_t ng, const std::vector<uint32_t>* lists, int nw, WaveSplit* ws,
+                      std::vector<char>* cut) {
+    cut->assign(ng, nw > 1 ? 1 : 0);
+    if (nw <= 1) return;
+    constexpr double kMeet = 1.5;
+    std::vector<size_t> ends;
+    for (size_t j = 0; j < ng;) {
+        size_t j2 = j + 1;
+        const uint32_t key = gates[j].x & ~gates[j].pd;
+        while (j2 < ng && (gates[j2].x & ~gates[j2].pd) == key) ++j2;
+        if (j2 - j > 1) {
+            const double one = kMeet + ws->passes(gates + j, lists + j, j2 - j, nw);
+            double shared = 0.0, single = 0.0;
+            ends.clear();
+            for (size_t k = j; k < j2;) {
+                uint32_t common = gates[k].pd;
+                size_t k2 = k + 1;
+                while (k2 < j2 && (common & gates[k2].pd)) common &= gates[k2++].pd;
+                shared += kMeet + ws->passes(gates + k, lists + k, k2 - k, nw);
+                ends.push_back(k2 - 1);
+                k = k2;
+            }
+            for (size_t k = j; k < j2; ++k) single += kMeet + double((lists[k].size() + size_t(nw) * 64 - 1) / (size_t(nw) * 64));
+            if (std::min(one, shared) <= single)
+                std::fill(cut->begin() + ptrdiff_t(j), cut->begin() + ptrdiff_t(j2 - 1), 0);
+            if (shared < one && shared <= single)
+                for (size_t k : ends) (*cut)[k] = 1;
+        }
+        j = j2;
+    }
+}
+
 // Smallest block-bit count for which every gate of A can run on the packed
 // layout (all excitations, annihilated orbitals in the low bits) and the
 // reference of ne electrons is entry 0 (block 0), or -1.
@@ -1847,10 +2010,13 @@ static int packed_min_L(const vqe_ansatz* A, int ne) {
     return std::max(1, ne);   // the reference in block 0
 }
 
+// ordered: the gates are applied one after the other by the run kernels, else
+// (pool sweeps, persistent passes) their lists are only walked, from the first
+// entry to the padding.
 static int packed_plan(const vqe_ansatz* A, DevAnsatz* da, const PackedLayout& lay,
-                       const Tuning& tn, PackedPlan** out) {
+                       const Tuning& tn, bool ordered, PackedPlan** out) {
     std::lock_guard<std::mutex> lk(A->mu);
-    const auto pkey = std::make_tuple(lay.L, tn.fwd_threads, tn.adj_threads, tn.tile_cap);
+    const auto pkey = std::make_tuple(lay.L, tn.fwd_threads, tn.adj_threads, tn.tile_cap, ordered);
     auto it = da->packed.find(pkey);
     if (it != da->packed.end()) {
         *out = it->second;
@@ -1866,6 +2032,12 @@ static int packed_plan(const vqe_ansatz* A, DevAnsatz* da, const PackedLayout& l
     std::vector<PackedGate> pg;
     std::vector<int2> info;       // per run and first-block class: {offset, stride}
     std::vector<uint32_t> ent;    // pair lists
+    WaveSplit split;
+    uint16_t low_a[128], low_b[128];   // the low strings, compact
+    for (int i = 0; i < 128; ++i) {
+        low_a[i] = uint16_t(compact_even_host(T.unA[i]));
+        low_b[i] = uint16_t(compact_even_host(T.unB[i] >> 1));
+    }
     std::vector<size_t> info0;    // offset of each run's info table
     // blocks that may hold a nonzero amplitude in the forward pass: first the
     // reference's (entry 0, the lowest nonempty block), then every block of a
@@ -2019,9 +2191,11 @@ static int packed_plan(const vqe_ansatz* A, DevAnsatz* da, const PackedLayout& l
             delete p;
             return fail(VQE_EINVAL, "packed layout: tile too large for the pair lists");
         }
+        r.max_entries = maxe;
+        r.idle = pair_entry(maxe, maxe + 1);
         info0.push_back(info.size());
         // pair lists per (gate, class); laid out per class with every gate's
-        // list padded to the class's longest (kPairNone), so that gate g's list
+        // list padded to the class's longest, so that gate g's list
         // starts at offset + g * stride and needs no per-gate descriptor
         const int64_t ng = j2 - j;
         const int ncl = r.ncls;
@@ -2057,45 +2231,142 @@ static int packed_plan(const vqe_ansatz* A, DevAnsatz* da, const PackedLayout& l
                     const uint32_t par_hi = uint32_t(__builtin_popcount((r.blk[b] << L) & h.chain & ~lowmask) & 1);
                     const int cB0 = T.offB[kB[b] + 1] - T.offB[kB[b]];
                     const int cB1 = T.offB[kB[be] + 1] - T.offB[kB[be]];
-                    for (int e = 0; e < cnt[b]; ++e) {   // D entries of the block, rank order
-                        const uint32_t rd = uint32_t(T.unA[T.offA[kA[b]] + e / cB0] | T.unB[T.offB[kB[b]] + e % cB0]);
-                        if ((rd & (pd | klo)) != pd) continue;
-                        const uint32_t re = rd ^ pd ^ klo;
-                        const int ie = off[be] + int(T.rankA[compact_even_host(re)]) * cB1 +
-                                       int(T.rankB[compact_even_host(re >> 1)]);
-                        const uint32_t par = (uint32_t(__builtin_popcount(rd & chlo)) + par_hi) & 1u;
-                        lst.push_back(uint32_t(off[b] + e) | (uint32_t(ie) << kEntBits) | (par << kEntParity));
+                    const uint32_t x = pd ^ klo;
+                    // the block's beta strings of D entries, then its alpha ones:
+                    // {D's rank, E's rank, parity}
+                    int col[128][3], ncol = 0;
+                    for (int i = 0; i < cB0; ++i) {
+                        const uint32_t rb = T.unB[T.offB[kB[b]] + i];
+                        if ((rb & x & 0xAAAAAAAAu) != (pd & 0xAAAAAAAAu)) continue;
+                        col[ncol][0] = i;
+                        col[ncol][1] = T.rankB[compact_even_host((rb ^ x) >> 1)];
+                        col[ncol++][2] = __builtin_popcount(rb & chlo);
                     }
+                    size_t at = lst.size();
+                    lst.resize(at + size_t(ncol) * size_t(cnt[b] / cB0));
+                    for (int i = 0; i < (ncol ? cnt[b] / cB0 : 0); ++i) {
+                        const uint32_t ra = T.unA[T.offA[kA[b]] + i];
+                        if ((ra & x & 0x55555555u) != (pd & 0x55555555u)) continue;
+                        const int e0 = off[b] + i * cB0, e1 = off[be] + int(T.rankA[compact_even_host(ra ^ x)]) * cB1;
+                        const uint32_t par = uint32_t(__builtin_popcount(ra & chlo)) + par_hi;
+                        for (int c = 0; c < ncol; ++c) {   // D and E, swapped for an odd parity
+                            const uint32_t d = uint32_t(e0 + col[c][0]), e = uint32_t(e1 + col[c][1]);
+                            lst[at++] = (par + uint32_t(col[c][2])) & 1u ? e | d << 16 : d | e << 16;
+                        }
+                    }
+                    lst.resize(at);
                 }
                 // pair updates of the gate over the run's live tiles of this class
                 p->pairs += double(lists[size_t(k - j) * ncl + cls].size() - list_before) * double(live_cls[size_t(cls)]);
             }
         }
-        for (int cls = 0; cls < ncl; ++cls) {
-            int2 rec = make_int2(int(ent.size()), 0);
-            if (used[size_t(cls)]) {
-                size_t stride = 0;
-                for (int64_t g = 0; g < ng; ++g) stride = std::max(stride, lists[size_t(g) * ncl + cls].size());
-                for (int64_t g = 0; g < ng; ++g) {
-                    const std::vector<uint32_t>& lst = lists[size_t(g) * ncl + cls];
-                    ent.insert(ent.end(), lst.begin(), lst.end());
-                    ent.insert(ent.end(), stride - lst.size(), kPairNone);
-                }
-                rec.y = int(stride);
-                p->max_stride = std::max(p->max_stride, int(stride));
-            }
-            info.push_back(rec);
-        }
-        if (ent.size() > size_t(1) << 31) {
-            delete p;
-            return fail(VQE_ERANGE, "packed layout: pair lists too large");
-        }
+        // the division among waves, by the class with the most pairs
         r.shape = packed_shape((maxe + 1) / 2, tn.fwd_threads);
         r.shape_adj = packed_shape((maxe + 1) / 2, tn.adj_threads);
-        r.max_entries = maxe;
         if (r.shape < 0 || r.shape_adj < 0) {
             delete p;
             return fail(VQE_EINVAL, "packed layout: tile too large for the run kernels");
+        }
+        const int nw_max = std::min(packed_shape_threads(r.shape), packed_shape_threads(r.shape_adj)) / 64;
+        std::vector<size_t> longest(size_t(ncl), 0);
+        std::vector<std::vector<uint32_t>> by_class(size_t(ng) * size_t(ncl));   // a class's lists together
+        size_t most = 0;
+        int heavy = 0;
+        for (int cls = 0; cls < ncl; ++cls) {
+            size_t sum = 0;
+            for (int64_t g = 0; g < ng; ++g) {
+                std::vector<uint32_t>& l = by_class[size_t(cls) * size_t(ng) + size_t(g)];
+                l.swap(lists[size_t(g) * ncl + cls]);
+                longest[size_t(cls)] = std::max(longest[size_t(cls)], l.size());
+                sum += l.size();
+            }
+            if (sum > most) {
+                most = sum;
+                heavy = cls;
+            }
+        }
+        auto waves_of = [&](int cls) {   // (48 of 64 lanes: the division is not even)
+            return !ordered ? 1 : std::max(1, std::min(nw_max, int((longest[size_t(cls)] + 47) / 48)));
+        };
+        auto strings = [&](int cls) {   // of the class's tile entries, without the bits that all share
+            split.blocks.clear();
+            split.low = L;
+            const int ca = cls / r.cls_b, cb = cls % r.cls_b;
+            for (int b = 0; b < r.nblk; ++b) {
+                const uint32_t hi = r.blk[b] << L;
+                const int kA = lay.na - ca - __builtin_popcount(hi & 0x55555555u);
+                const int kB = lay.nb - cb - __builtin_popcount(hi & 0xAAAAAAAAu);
+                if (kA < 0 || kA > T.La || kB < 0 || kB > T.Lb) continue;
+                split.blocks.push_back({hi, low_a + T.offA[kA], low_b + T.offB[kB], T.offA[kA + 1] - T.offA[kA],
+                                        T.offB[kB + 1] - T.offB[kB]});
+            }
+        };
+        std::vector<char> cut(size_t(ng), 1);
+        const GateDesc* gates = A->gates.data() + j;
+        if (ordered) {
+            strings(heavy);
+            wave_cuts(gates, size_t(ng), &by_class[size_t(heavy) * size_t(ng)], waves_of(heavy), &split, &cut);
+        }
+        for (int pass = 0; pass < 2; ++pass) {
+            const size_t ent0 = ent.size(), inf0 = info.size();
+            bool fits = true;
+            for (int cls = 0; cls < ncl && fits; ++cls) {
+                int2 rec = make_int2(int(ent.size()), 0);
+                if (used[size_t(cls)] && longest[size_t(cls)] > 0) {
+                    const std::vector<uint32_t>* l = &by_class[size_t(cls) * size_t(ng)];
+                    const int nw = waves_of(cls);
+                    if (nw > 1) strings(cls);
+                    size_t passes = (longest[size_t(cls)] + size_t(nw) * 64 - 1) / (size_t(nw) * 64);
+                    const size_t at = ent.size();
+                    // rows for the passes of an even division, widened where a
+                    // stretch needs more
+                    size_t stride = passes * 64 * size_t(nw);
+                    ent.resize(at + size_t(ng) * stride, r.idle);
+                    for (size_t g = 0; g < size_t(ng) && fits;) {
+                        size_t g2 = g + 1;
+                        while (!cut[g2 - 1] && g2 < size_t(ng)) ++g2;
+                        split.set(gates + g, l + g, g2 - g, nw);
+                        for (; g < g2 && fits; ++g) {
+                            uint32_t c[16];
+                            split.count(l[g], c);
+                            const size_t need = (*std::max_element(c, c + nw) + 63) / 64;
+                            if (need > passes) {
+                                const size_t old = stride;
+                                passes = need;
+                                stride = passes * 64 * size_t(nw);
+                                fits = stride < 65536;
+                                if (!fits) break;
+                                ent.resize(at + size_t(ng) * stride, r.idle);
+                                for (size_t k = g; k-- > 0;) {
+                                    uint32_t* o = ent.data() + at;
+                                    std::copy_backward(o + k * old, o + (k + 1) * old, o + k * stride + old);
+                                    std::fill(o + k * stride + old, o + (k + 1) * stride, r.idle);
+                                }
+                                std::fill(ent.begin() + ptrdiff_t(at + g * stride), ent.end(), r.idle);
+                            }
+                            split.place(l[g], ent.data() + at + g * stride);
+                        }
+                    }
+                    rec.y = int(stride) | nw << 16;
+                    if (!fits) break;
+                    p->max_stride = std::max(p->max_stride, rec.y & 0xffff);
+                }
+                info.push_back(rec);
+            }
+            if (fits) break;
+            ent.resize(ent0);   // one wave's share is too long: gate by gate
+            info.resize(inf0);
+            std::fill(cut.begin(), cut.end(), 1);
+        }
+        for (int64_t g = 0; g + 1 < ng; ++g)
+            if (cut[size_t(g)]) {
+                r.meet_fwd[g / 64] |= uint64_t(1) << (g % 64);
+                const int64_t t = ng - 2 - g;
+                r.meet_adj[t / 64] |= uint64_t(1) << (t % 64);
+            }
+        if (ent.size() > size_t(1) << 31) {
+            delete p;
+            return fail(VQE_ERANGE, "packed layout: pair lists too large");
         }
         p->off.push_back(int(pg.size()));
         for (int64_t k = j; k < j2; ++k) {
@@ -2110,7 +2381,7 @@ static int packed_plan(const vqe_ansatz* A, DevAnsatz* da, const PackedLayout& l
             p->gcnt[size_t(k)] = r.ntiles;
         }
         p->gstride = std::max(p->gstride, r.ntiles);
-        p->max_lds = std::max(p->max_lds, (size_t(maxe) * 2 + 2 * size_t(ng)) * sizeof(double2));
+        p->max_lds = std::max(p->max_lds, (size_t(maxe + 2) * 2 + 2 * size_t(ng)) * sizeof(double2) + size_t(ng) * 16 * sizeof(double));
         p->max_entries = std::max(p->max_entries, maxe);
         p->max_gates = std::max(p->max_gates, int(ng));
         p->run_work.push_back(double(moved_live) * double(ng));
@@ -2122,9 +2393,9 @@ static int packed_plan(const vqe_ansatz* A, DevAnsatz* da, const PackedLayout& l
         }
         tdesc0.push_back(tdesc.size());
         if (live_of.back().second == kNoList)
-            for (int32_t o = 0; o < r.ntiles; ++o) tdesc.push_back(host_tile_desc(T, r, o, lay.base));
+            for (int32_t o = 0; o < r.ntiles; ++o) tdesc.push_back(host_tile_desc(T, r, o, lay.base, info.data() + info0.back()));
         else
-            for (size_t i = live0; i < live_all.size(); ++i) tdesc.push_back(host_tile_desc(T, r, live_all[i], lay.base));
+            for (size_t i = live0; i < live_all.size(); ++i) tdesc.push_back(host_tile_desc(T, r, live_all[i], lay.base, info.data() + info0.back()));
         p->fwd_bytes += 2.0 * double(sizeof(double2)) * double(moved_live);
         p->adj_bytes += 4.0 * double(sizeof(double2)) * double(moved_live);   // live tiles, as the forward
         p->sweep_bytes += 2.0 * double(sizeof(double2)) * double(moved);
@@ -2135,14 +2406,16 @@ static int packed_plan(const vqe_ansatz* A, DevAnsatz* da, const PackedLayout& l
     int rc = upload(&p->d_gates, pg.data(), pg.size());
     if (!rc) rc = upload(&p->d_gcnt, p->gcnt.data(), p->gcnt.size());
     if (!rc) rc = upload(&p->d_info, info.data(), info.size());
-    if (!rc) rc = upload(&p->d_ent, ent.data(), ent.size());
+    const size_t ahead = size_t(kListAhead) * size_t(p->max_stride);   // the kernels read past both ends
+    ent.insert(ent.end(), ahead, 0u);
+    if (!rc) rc = upload(&p->d_ent, ent.data(), ent.size(), ahead);
     if (!rc) rc = upload(&p->d_live, live_all.data(), live_all.size());
     if (!rc) rc = upload(&p->d_tdesc, tdesc.data(), tdesc.size());
     std::vector<int32_t> gcnt_live(p->gcnt);
     if (!rc)
         for (size_t r = 0; r < p->runs.size(); ++r) {
             p->runs[r].info = p->d_info + info0[r];
-            p->runs[r].ent = p->d_ent;
+            p->runs[r].ent = p->d_ent + ahead;
             const bool listed = live_of[r].second != kNoList && p->d_live != nullptr;
             p->runs[r].live = listed ? p->d_live + live_of[r].first : nullptr;
             p->runs[r].nlive = listed ? int32_t(live_of[r].second) : p->runs[r].ntiles;
@@ -2676,7 +2949,7 @@ static int make_eval_plan(const vqe_ansatz* A, int ne, bool batched, EvalPlan* e
         }
         if (ep->packed) {
             if (int rc = packed_layout(n, ne, ep->hx.L, &ep->lay)) return rc;
-            if (int rc = packed_plan(A, da, *ep->lay, tn, &ep->pp)) return rc;
+            if (int rc = packed_plan(A, da, *ep->lay, tn, force_L == 0, &ep->pp)) return rc;
             // the persistent passes (force_L) store a partial by tile, the runs
             // by position in the live list
             ep->gstride = force_L > 0 ? ep->pp->gstride : ep->pp->gstride_live;
@@ -3646,7 +3919,7 @@ int pool_gradient_impl(const vqe_hamiltonian* H, const vqe_ansatz* A, const vqe_
         const int need = packed_min_L(pool, ne);
         if (need < 0 || need > probe.hx.L || !pool->sector_conserving)
             return fail(VQE_EINVAL, "pool does not fit the packed sector evaluation of this ansatz");
-        if (int rc = packed_plan(pool, dp, *probe.lay, tn, &ppool)) return rc;
+        if (int rc = packed_plan(pool, dp, *probe.lay, tn, false, &ppool)) return rc;
         if (int rc = pool_sweep(pool, ppool, &psw)) return rc;
     } else {
         if (int rc = get_plan(pool, dp, tn, &apool)) return rc;
