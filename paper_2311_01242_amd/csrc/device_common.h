@@ -766,22 +766,24 @@ int blocks_for(uint64_t work);
 // ------------------------------------------------- whole-state passes
 //
 // Sectors that fit one compute unit's LDS (k_whole.hip): amplitudes in
-// string-product order.  A pair's entry is two words, 8 times the indices of D
-// and E, swapped where the pair's sign is negative; threads without a pair have
-// two of the kWholeIdle dummies after the amplitudes.
+// string-product order.  A pair's entry is the indices of D and E (first in the
+// low half), swapped where the pair's sign is negative; places without a pair
+// have two of the kWholeIdle dummies after the amplitudes.
 constexpr int kWholeMax = 10000;   // amplitudes: phi and lambda side by side in 160 KiB
 constexpr int kWholeIdle = 128;
+constexpr int kWholePlaces = 4;    // most places per thread of a gate step without waits
+constexpr int kWholeWaves = 16;    // most waves of a pass (the gradient's partials per gate)
 
-// Consecutive gates [g0, g1) of one kind: passes == 0, narrow (at most
-// `threads` pairs each), else wide (threads * passes).  ent: their first
-// entry.
+// Consecutive gates [g0, g1) with `passes` places per thread each.  ent: their
+// first entry.
 struct WholeSeg {
     int32_t g0, g1, passes, ent;
 };
 
 struct WholeArgs {
-    const uint32_t* ent;     // two words per entry
+    const uint32_t* ent;     // (readable kListAhead rows of kWholePlaces places past both ends)
     const WholeSeg* seg;
+    const uint32_t* meet;    // bit j + 8: the waves meet between gates j and j + 1
     int32_t nseg, nE, M;
     int32_t threads;         // launch shape
     int32_t ref, ref_neg;    // the reference's index; its amplitude is -1

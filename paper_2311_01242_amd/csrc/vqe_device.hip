@@ -277,6 +277,7 @@ struct WholePlan {
     WholeArgs args{};            // threads == 0: the state does not fit
     uint32_t* d_ent = nullptr;
     WholeSeg* d_seg = nullptr;
+    uint32_t* d_meet = nullptr;
     double pairs = 0.0;          // pair updates of one pass over the gates
 };
 
@@ -1731,112 +1732,6 @@ static int ci_matrix(const vqe_hamiltonian* H, CiHam* c, const CiSpace& cs, cons
 }
 
 
-// Pairs of gate g (D in the sector: annihilated orbitals occupied, created ones
-// empty) as alpha pairs times beta pairs: appended are (D's row, E's row, sign)
-// and (D's column, E's column, sign); with `sgn` the signs include the matrix
-// form's amplitude signs of D and E.
-struct SpinPair {
-    int d, e, par;
-};
-static void whole_pairs(const GateDesc& g, const CiSpace& cs, bool sgn, std::vector<SpinPair>* rows,
-                        std::vector<SpinPair>* cols) {
-    const uint32_t xa = compact_even_host(g.x), xb = compact_even_host(g.x >> 1);
-    const uint32_t da = compact_even_host(g.pd), db = compact_even_host(g.pd >> 1);
-    const uint32_t ca = compact_even_host(g.chain), cb = compact_even_host(g.chain >> 1);
-    uint32_t Ma = 0, Mb = 0;   // amplitude signs: s(D) s(E) = (-1)^{|b_E & Mb| + |a_D & Ma|}
-    if (sgn) {
-        for (int u = 0; u < cs.ob; ++u)
-            if (__builtin_popcount(xa >> (u + 1)) & 1) Mb |= 1u << u;
-        for (int t = 0; t < cs.oa; ++t)
-            if (__builtin_popcount(xb & ((1u << t) - 1u)) & 1) Ma |= 1u << t;
-    }
-    rows->clear();
-    cols->clear();
-    for (int ia = 0; ia < cs.NA; ++ia) {
-        const uint32_t a = cs.sa[size_t(ia)];
-        if ((a & xa) != da) continue;
-        rows->push_back({ia, cs.rank_a[a ^ xa], (__builtin_popcount(a & ca) + __builtin_popcount(a & Ma)) & 1});
-    }
-    for (int ib = 0; ib < cs.NB; ++ib) {
-        const uint32_t b = cs.sb[size_t(ib)];
-        if ((b & xb) != db) continue;
-        cols->push_back({ib, cs.rank_b[b ^ xb], (__builtin_popcount(b & cb) + __builtin_popcount((b ^ xb) & Mb)) & 1});
-    }
-}
-
-static int whole_plan(const vqe_ansatz* A, DevAnsatz* da, const CiSpace& cs, uint32_t ref, bool sgn,
-                      const WholePlan** out) {
-    std::lock_guard<std::mutex> lk(A->mu);
-    const auto key = std::make_pair(&cs, sgn ? 1 : 0);
-    auto it = da->whole.find(key);
-    if (it != da->whole.end()) {
-        *out = it->second;
-        return VQE_OK;
-    }
-    const size_t M = A->gates.size();
-    std::vector<int> cnt(M);
-    std::vector<SpinPair> rows, cols;
-    for (size_t j = 0; j < M; ++j) {
-        whole_pairs(A->gates[j], cs, false, &rows, &cols);
-        cnt[j] = int(rows.size() * cols.size());
-    }
-    auto* p = new WholePlan();
-    for (int c : cnt) p->pairs += c;
-    WholeArgs& w = p->args;
-    w.nE = cs.NA * cs.NB;
-    w.M = int32_t(M);
-    int threads = 0;
-    if (whole_prepare(w.nE, w.M, cnt.data(), &threads) == 0) {
-        std::vector<uint32_t> ent;
-        std::vector<WholeSeg> seg;
-        for (size_t j = 0; j < M;) {
-            const bool wide = cnt[j] > threads;
-            size_t j2 = j;
-            int most = 0;
-            while (j2 < M && (cnt[j2] > threads) == wide) most = std::max(most, cnt[j2++]);
-            const int passes = wide ? (most + threads - 1) / threads : 1;
-            seg.push_back(WholeSeg{int32_t(j), int32_t(j2), wide ? passes : 0, int32_t(ent.size() / 2)});
-            for (; j < j2; ++j) {
-                whole_pairs(A->gates[j], cs, sgn, &rows, &cols);
-                const int neg = A->gates[j].csign < 0.0 ? 1 : 0;
-                for (const SpinPair& r : rows)
-                    for (const SpinPair& c : cols) {
-                        const uint32_t d = 8u * uint32_t(r.d * cs.NB + c.d), e = 8u * uint32_t(r.e * cs.NB + c.e);
-                        const bool swap = (r.par + c.par + neg) & 1;
-                        ent.push_back(swap ? e : d);
-                        ent.push_back(swap ? d : e);
-                    }
-                for (int k = cnt[j]; k < passes * threads; ++k) {   // a lane's own dummy pair
-                    const uint32_t idle = 8u * uint32_t(w.nE + 2 * (k & 63));
-                    ent.push_back(idle);
-                    ent.push_back(idle + 8u);
-                }
-            }
-        }
-        const uint32_t ra = compact_even_host(ref), rb = compact_even_host(ref >> 1);
-        w.ref = cs.rank_a[ra] * cs.NB + cs.rank_b[rb];
-        int cross = 0;   // alpha orbitals after a beta one
-        for (uint32_t m = rb; sgn && m; m &= m - 1)
-            cross += __builtin_popcount(ra & ~((2u << __builtin_ctz(m)) - 1u));
-        w.ref_neg = cross & 1;
-        int rc = upload(&p->d_ent, ent.data(), ent.size());
-        if (!rc) rc = upload(&p->d_seg, seg.data(), seg.size());
-        if (rc) {
-            (void)hipFree(p->d_ent);
-            (void)hipFree(p->d_seg);
-            delete p;
-            return rc;
-        }
-        w.ent = p->d_ent;
-        w.seg = p->d_seg;
-        w.nseg = int32_t(seg.size());
-        w.threads = threads;
-    }
-    da->whole[key] = p;
-    *out = p;
-    return VQE_OK;
-}
-
 // Division of consecutive gates' pairs (a | b << 16 each) among waves such that
 // no amplitude is touched by two waves.  The gates leave the bits outside their
 // orbitals as they are, so the strings with equal bits there form a group that
@@ -1946,12 +1841,13 @@ struct WaveSplit {
         }
         return *std::max_element(most, most + nw);
     }
-    // A gate's list with a place of 64 entries per wave and pass.
-    void place(const std::vector<uint32_t>& list, uint32_t* out) const {
+    // A gate's list, indices times 2^shift, with a place of 64 entries per wave
+    // and pass.
+    void place(const std::vector<uint32_t>& list, uint32_t* out, int shift) const {
         uint32_t c[16] = {};
         for (size_t i = 0; i < list.size(); ++i) {
             const uint32_t w = of(list[i], i), k = c[w]++;
-            out[((k >> 6) * uint32_t(nw) + w) * 64 + (k & 63u)] = list[i] << 3;
+            out[((k >> 6) * uint32_t(nw) + w) * 64 + (k & 63u)] = list[i] << shift;
         }
     }
 };
@@ -1974,10 +1870,10 @@ static void wave_cuts(const GateDesc* gates, size_t ng, const std::vector<uint32
         const uint32_t key = gates[j].x & ~gates[j].pd;
         while (j2 < ng && (gates[j2].x & ~gates[j2].pd) == key) ++j2;
         if (j2 - j > 1) {
-            const double one = kMeet + ws->passes(gates + j, lists + j, j2 - j, nw);
+            const double one = kMeet + ws->passes(gates + j, lists + j, j2 - j, nw), least = kMeet + double(j2 - j);
             double shared = 0.0, single = 0.0;
             ends.clear();
-            for (size_t k = j; k < j2;) {
+            for (size_t k = j; one > least && k < j2;) {
                 uint32_t common = gates[k].pd;
                 size_t k2 = k + 1;
                 while (k2 < j2 && (common & gates[k2].pd)) common &= gates[k2++].pd;
@@ -1986,6 +1882,7 @@ static void wave_cuts(const GateDesc* gates, size_t ng, const std::vector<uint32
                 k = k2;
             }
             for (size_t k = j; k < j2; ++k) single += kMeet + double((lists[k].size() + size_t(nw) * 64 - 1) / (size_t(nw) * 64));
+            if (one <= least) shared = single = one;
             if (std::min(one, shared) <= single)
                 std::fill(cut->begin() + ptrdiff_t(j), cut->begin() + ptrdiff_t(j2 - 1), 0);
             if (shared < one && shared <= single)
@@ -1993,6 +1890,155 @@ static void wave_cuts(const GateDesc* gates, size_t ng, const std::vector<uint32
         }
         j = j2;
     }
+}
+
+// Pairs of gate g (D in the sector: annihilated orbitals occupied, created ones
+// empty) as alpha pairs times beta pairs: appended are (D's row, E's row, sign)
+// and (D's column, E's column, sign); with `sgn` the signs include the matrix
+// form's amplitude signs of D and E.
+struct SpinPair {
+    int d, e, par;
+};
+static void whole_pairs(const GateDesc& g, const CiSpace& cs, bool sgn, std::vector<SpinPair>* rows,
+                        std::vector<SpinPair>* cols) {
+    const uint32_t xa = compact_even_host(g.x), xb = compact_even_host(g.x >> 1);
+    const uint32_t da = compact_even_host(g.pd), db = compact_even_host(g.pd >> 1);
+    const uint32_t ca = compact_even_host(g.chain), cb = compact_even_host(g.chain >> 1);
+    uint32_t Ma = 0, Mb = 0;   // amplitude signs: s(D) s(E) = (-1)^{|b_E & Mb| + |a_D & Ma|}
+    if (sgn) {
+        for (int u = 0; u < cs.ob; ++u)
+            if (__builtin_popcount(xa >> (u + 1)) & 1) Mb |= 1u << u;
+        for (int t = 0; t < cs.oa; ++t)
+            if (__builtin_popcount(xb & ((1u << t) - 1u)) & 1) Ma |= 1u << t;
+    }
+    rows->clear();
+    cols->clear();
+    for (int ia = 0; ia < cs.NA; ++ia) {
+        const uint32_t a = cs.sa[size_t(ia)];
+        if ((a & xa) != da) continue;
+        rows->push_back({ia, cs.rank_a[a ^ xa], (__builtin_popcount(a & ca) + __builtin_popcount(a & Ma)) & 1});
+    }
+    for (int ib = 0; ib < cs.NB; ++ib) {
+        const uint32_t b = cs.sb[size_t(ib)];
+        if ((b & xb) != db) continue;
+        cols->push_back({ib, cs.rank_b[b ^ xb], (__builtin_popcount(b & cb) + __builtin_popcount((b ^ xb) & Mb)) & 1});
+    }
+}
+
+static int whole_plan(const vqe_ansatz* A, DevAnsatz* da, const CiSpace& cs, uint32_t ref, bool sgn,
+                      const WholePlan** out) {
+    std::lock_guard<std::mutex> lk(A->mu);
+    const auto key = std::make_pair(&cs, sgn ? 1 : 0);
+    auto it = da->whole.find(key);
+    if (it != da->whole.end()) {
+        *out = it->second;
+        return VQE_OK;
+    }
+    const size_t M = A->gates.size();
+    std::vector<int> cnt(M);
+    std::vector<SpinPair> rows, cols;
+    for (size_t j = 0; j < M; ++j) {
+        whole_pairs(A->gates[j], cs, false, &rows, &cols);
+        cnt[j] = int(rows.size() * cols.size());
+    }
+    auto* p = new WholePlan();
+    for (int c : cnt) p->pairs += c;
+    WholeArgs& w = p->args;
+    w.nE = cs.NA * cs.NB;
+    w.M = int32_t(M);
+    int threads = 0;
+    if (whole_prepare(w.nE, w.M, cnt.data(), &threads) == 0) {
+        const int nw = threads / 64;
+        std::vector<std::vector<uint32_t>> lists(M);
+        for (size_t j = 0; j < M; ++j) {
+            whole_pairs(A->gates[j], cs, sgn, &rows, &cols);
+            const int neg = A->gates[j].csign < 0.0 ? 1 : 0;
+            lists[j].reserve(size_t(cnt[j]));
+            for (const SpinPair& r : rows)
+                for (const SpinPair& c : cols) {
+                    const uint32_t d = uint32_t(r.d * cs.NB + c.d), e = uint32_t(r.e * cs.NB + c.e);
+                    lists[j].push_back((r.par + c.par + neg) & 1 ? e | d << 16 : d | e << 16);
+                }
+        }
+        WaveSplit split;
+        std::vector<uint16_t> sa(cs.sa.begin(), cs.sa.end()), sb(cs.sb.begin(), cs.sb.end());
+        split.low = cs.oa + cs.ob;
+        split.blocks.push_back({0u, sa.data(), sb.data(), cs.NA, cs.NB});
+        std::vector<char> cut;
+        if (nw < kWholeWaves) wave_cuts(A->gates.data(), M, lists.data(), nw, &split, &cut);
+        else cut.assign(M, 1);
+        // a gate's passes: the most of a wave
+        std::vector<int> passes(M);
+        auto stretches = [&](auto&& f) {
+            for (size_t j = 0; j < M;) {
+                size_t j2 = j + 1;
+                while (j2 < M && !cut[j2 - 1]) ++j2;
+                split.set(&A->gates[j], &lists[j], j2 - j, nw);
+                for (; j < j2; ++j) f(j);
+            }
+        };
+        std::vector<uint32_t> ent;
+        std::vector<size_t> at(M);
+        const uint32_t idle = uint32_t(w.nE) | uint32_t(w.nE + 1) << 16;
+        stretches([&](size_t j) {   // placed apart, then moved to their segments' rows
+            uint32_t c[16];
+            split.count(lists[j], c);
+            passes[j] = std::max(1, int((*std::max_element(c, c + nw) + 63) / 64));
+            at[j] = ent.size();
+            ent.resize(ent.size() + size_t(passes[j]) * size_t(threads), idle);
+            split.place(lists[j], ent.data() + at[j], 0);
+        });
+        const size_t ahead = size_t(kListAhead) * size_t(kWholePlaces) * size_t(threads);
+        std::vector<uint32_t> laid;
+        laid.reserve(ent.size() + ahead);
+        std::vector<WholeSeg> seg;
+        for (int& x : passes)   // places: 1, 2 or 4 where the kernel has a loop for them
+            if (x == 3 && threads <= 256) x = 4;
+        for (size_t j = 0; j < M;) {
+            // gates of as many places, and short stretches of fewer between them
+            constexpr size_t kShort = 16;
+            const int most = passes[j];
+            size_t j2 = j + 1, end = j + 1;
+            while (j2 < M && passes[j2] <= most && j2 - end < kShort)
+                if (passes[j2++] == most) end = j2;
+            if (j2 == M && j2 - end < kShort) end = M;
+            seg.push_back(WholeSeg{int32_t(j), int32_t(end), most, int32_t(laid.size())});
+            for (; j < end; ++j) {
+                const auto from = ent.begin() + ptrdiff_t(at[j]);
+                const size_t have = std::min(size_t(most) * size_t(threads), (j + 1 < M ? at[j + 1] : ent.size()) - at[j]);
+                laid.insert(laid.end(), from, from + ptrdiff_t(have));
+                laid.insert(laid.end(), size_t(most) * size_t(threads) - have, idle);
+            }
+        }
+        laid.insert(laid.end(), ahead, idle);
+        std::vector<uint32_t> meet((M + 8 + 31) / 32 + 2, 0u);
+        for (size_t j = 0; j + 1 < M; ++j)
+            if (cut[j]) meet[(j + 8) / 32] |= 1u << ((j + 8) % 32);
+        const uint32_t ra = compact_even_host(ref), rb = compact_even_host(ref >> 1);
+        w.ref = cs.rank_a[ra] * cs.NB + cs.rank_b[rb];
+        int cross = 0;   // alpha orbitals after a beta one
+        for (uint32_t m = rb; sgn && m; m &= m - 1)
+            cross += __builtin_popcount(ra & ~((2u << __builtin_ctz(m)) - 1u));
+        w.ref_neg = cross & 1;
+        int rc = upload(&p->d_ent, laid.data(), laid.size(), ahead);
+        if (!rc) rc = upload(&p->d_seg, seg.data(), seg.size());
+        if (!rc) rc = upload(&p->d_meet, meet.data(), meet.size());
+        if (rc) {
+            (void)hipFree(p->d_ent);
+            (void)hipFree(p->d_seg);
+            (void)hipFree(p->d_meet);
+            delete p;
+            return rc;
+        }
+        w.ent = p->d_ent + ahead;
+        w.seg = p->d_seg;
+        w.meet = p->d_meet;
+        w.nseg = int32_t(seg.size());
+        w.threads = threads;
+    }
+    da->whole[key] = p;
+    *out = p;
+    return VQE_OK;
 }
 
 // Smallest block-bit count for which every gate of A can run on the packed
@@ -2344,7 +2390,7 @@ static int packed_plan(const vqe_ansatz* A, DevAnsatz* da, const PackedLayout& l
                                 }
                                 std::fill(ent.begin() + ptrdiff_t(at + g * stride), ent.end(), r.idle);
                             }
-                            split.place(l[g], ent.data() + at + g * stride);
+                            split.place(l[g], ent.data() + at + g * stride, 3);
                         }
                     }
                     rec.y = int(stride) | nw << 16;
@@ -2917,7 +2963,7 @@ static int make_eval_plan(const vqe_ansatz* A, int ne, bool batched, EvalPlan* e
         if (int rc = hx_tables(ep->hx.L, &ep->hxt)) return rc;
         ep->nblk_e = ep->hx.ntiles;
         // a sector that fits one workgroup: whole-state passes (faster at every
-        // size measured, e.g. 16 qubits, one state: 203 us of both passes against
+        // size measured, e.g. 16 qubits, one state: 192 us of both passes against
         // 369 with tiled runs), unless a largest tile below it was asked for
         if (ep->packed && whole_ok && g_packed_enabled.load() >= 2 && g_real_enabled.load() != 0 &&
             (n + 1) / 2 <= kCiMaxBits) {
@@ -2937,7 +2983,7 @@ static int make_eval_plan(const vqe_ansatz* A, int ne, bool batched, EvalPlan* e
                 ep->cspace = cs;
                 ep->ciargs = args;
                 ep->nblk_e = cs->NA * args.nsplit;
-                ep->gstride = 1;
+                ep->gstride = kWholeWaves;
                 ep->d_gcnt = nullptr;
                 ep->elems = size;
                 ep->fwd_bytes = 8.0 * double(size);         // phi written
@@ -3329,6 +3375,7 @@ vqe_ansatz::~vqe_ansatz() {
         for (auto& pl : kv.second->whole) {
             (void)hipFree(pl.second->d_ent);
             (void)hipFree(pl.second->d_seg);
+            (void)hipFree(pl.second->d_meet);
             delete pl.second;
         }
         for (auto& pl : kv.second->packed) {

@@ -44,7 +44,8 @@ def _paths(f, n, batched=False):
 
 
 @pytest.mark.parametrize("n,ne,kind", [(4, 2, "uccsd"), (5, 2, "last"), (7, 3, "uccsd"), (8, 4, "kup2"), (10, 5, "twice"),
-                                       (12, 6, "kup3"), (13, 6, "uccsd"), (14, 5, "uccsd"), (16, 8, "last"),
+                                       (12, 6, "kup3"), (13, 6, "uccsd"), (14, 5, "uccsd"), (14, 7, "twice"),
+                                       (15, 7, "uccsd"), (15, 8, "kup2"), (16, 8, "last"),
                                        (16, 8, "kup1"), (16, 9, "uccsd"), (17, 8, "uccsd")])
 def test_whole_state_passes(n, ne, kind):
     H = vq.Hamiltonian.from_integrals(n, *random_integrals(n, 3100 + n))
