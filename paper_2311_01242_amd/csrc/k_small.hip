@@ -45,6 +45,14 @@ struct SmallGate {
 };
 static_assert(sizeof(SmallGate) == 32, "SmallGate layout");
 
+// A term of the staged Hamiltonian: flip (bit 15: leads out of the sector)
+// and sign mask, and its table.
+struct SmallTerm {
+    uint32_t xw, pos;
+    int32_t tab;
+};
+static_assert(kSmallMaxN <= 15, "a term's masks have 15 bits");
+
 __host__ __device__ inline size_t small_r16(size_t v) { return (v + 15) & ~size_t(15); }
 
 // Threads per string in the H-apply.
@@ -120,24 +128,44 @@ __device__ __forceinline__ void small_stage_space(const SmallSpace& sp, uint32_t
     small_copy<NT>(rank, sp.rank, 2 * (size_t(1) << sp.n));
 }
 
-// Pair update of gate g on LDS amplitudes: psi <- U psi.
-template <typename V>
-__device__ __forceinline__ void small_gate(const SmallGate& g, const uint32_t* str, const int16_t* rank, int nsec,
-                                           V* psi) {
-    for (int t = threadIdx.x; t < nsec; t += kSmallThreads) {
-        const uint32_t d = str[t];
-        if ((d & g.x) != g.pd) continue;
-        const int re = rank[d ^ g.x];
-        const double ss = double(g.csign) * parity_sign(d & g.chain) * g.s;
-        V a = psi[t], b = psi[re];
-        givens(a, b, g.c, ss);
-        psi[t] = a;
-        psi[re] = b;
+// What a thread needs of a gate besides the amplitudes: the partner of each of
+// its KT strings (rank, or -1 when the string is no D of the gate) and the
+// sign.  It depends on nothing the gates change, so it is looked up one gate
+// ahead, beside the current gate's pairs: what bounds a step is its chain of
+// LDS reads (string, rank, amplitudes).  512 states of 11 orbitals and 7 pairs
+// (330 strings, 28 gates): forward 15.2 -> 13.3 us, reverse 19.3 -> 16.0; most of
+// the rest is the staging's loads.
+constexpr uint32_t kSmallNone = ~0u;
+template <int KT>
+struct SmallPairs {
+    double c, s;
+    int re[KT];
+    bool neg[KT];
+    __device__ __forceinline__ void find(const SmallGate& g, const uint32_t (&str)[KT], const int16_t* rank) {
+        c = g.c;
+        s = g.s;
+#pragma unroll
+        for (int k = 0; k < KT; ++k) {
+            const bool hit = str[k] != kSmallNone && (str[k] & g.x) == g.pd;
+            const int r = rank[hit ? str[k] ^ g.x : 0u];
+            re[k] = hit ? r : -1;
+            neg[k] = (__popc(str[k] & g.chain) & 1) != (g.csign < 0.0f);
+        }
+    }
+};
+
+// The thread's strings t, t + kSmallThreads, ...; kSmallNone past the sector.
+template <int KT>
+__device__ __forceinline__ void small_strings(const uint32_t* str, int nsec, uint32_t (&mine)[KT]) {
+#pragma unroll
+    for (int k = 0; k < KT; ++k) {
+        const int t = int(threadIdx.x) + k * kSmallThreads;
+        mine[k] = t < nsec ? str[t] : kSmallNone;
     }
 }
 
 // Forward pass: |ref> then U_M ... U_1; phi and the gates' (cos, sin) out.
-template <typename V>
+template <typename V, int KT>
 __global__ void __launch_bounds__(kSmallThreads) k_small_fwd(const StateDesc* __restrict__ sd, SmallSpace sp) {
     extern __shared__ __align__(16) unsigned char smem[];
     const SmallLayout L = small_layout(sp, kSmallFwd);
@@ -157,9 +185,24 @@ __global__ void __launch_bounds__(kSmallThreads) k_small_fwd(const StateDesc* __
         gs[j] = SmallGate{g.x, g.pd, g.chain, float(g.csign), c, sn};
     }
     __syncthreads();
+    uint32_t mine[KT];
+    small_strings<KT>(str, sp.nsec, mine);
+    SmallPairs<KT> cur, next;
+    if (s.M > 0) cur.find(gs[0], mine, rank);
     for (int j = 0; j < s.M; ++j) {
-        small_gate<V>(gs[j], str, rank, sp.nsec, psi);
+        next.find(gs[min(j + 1, s.M - 1)], mine, rank);
+#pragma unroll
+        for (int k = 0; k < KT; ++k) {
+            const int t = int(threadIdx.x) + k * kSmallThreads;
+            if (cur.re[k] >= 0) {
+                V a = psi[t], b = psi[cur.re[k]];
+                givens(a, b, cur.c, cur.neg[k] ? -cur.s : cur.s);
+                psi[t] = a;
+                psi[cur.re[k]] = b;
+            }
+        }
         __syncthreads();
+        cur = next;
     }
     V* phi = reinterpret_cast<V*>(s.phi);
     for (int t = threadIdx.x; t < sp.nsec; t += kSmallThreads) phi[t] = psi[t];
@@ -184,36 +227,64 @@ __global__ void __launch_bounds__(kSmallHxThreads) k_small_hx(const StateDesc* _
     const bool hlds = sp.ham_lds > 0 && small_ham_bytes(s.G, s.nsub, s.ntab) <= size_t(sp.ham_lds);
     double e = 0.0;
     if (hlds) {
-        GroupDesc* groups = reinterpret_cast<GroupDesc*>(smem + L.ham);
-        double* tabs = reinterpret_cast<double*>(smem + L.ham + 16 * size_t(s.G));
-        SubDesc* subs = reinterpret_cast<SubDesc*>(reinterpret_cast<unsigned char*>(tabs) +
-                                                   small_r16(8 * size_t(s.ntab)));
-        int32_t* sgrp = reinterpret_cast<int32_t*>(reinterpret_cast<unsigned char*>(subs) +
-                                                   small_r16(8 * size_t(s.nsub)));
-        small_copy<kSmallHxThreads>(groups, s.groups, 16 * size_t(s.G));
+        // a term is one record, read by all lanes at once; the terms of the
+        // group without a flip need only their sign and value, which is what
+        // most of a seniority-zero Hamiltonian's are.  Bound by the instructions
+        // of its 16 waves after the staging's loads (512 states of 330 strings:
+        // 26.8 us with group, subgroup and rank read for every term, 24.5 so)
+        double* tabs = reinterpret_cast<double*>(smem + L.ham);
+        SmallTerm* terms = reinterpret_cast<SmallTerm*>(smem + L.ham + small_r16(8 * size_t(s.ntab)));
         small_copy<kSmallHxThreads>(tabs, s.tabs, 8 * size_t(s.ntab));
-        small_copy<kSmallHxThreads>(subs, s.subs, 8 * size_t(s.nsub));
+        int* diag = reinterpret_cast<int*>(red);   // free until the energy's sum
+        if (threadIdx.x < 2) diag[threadIdx.x] = 0;
+        __syncthreads();
         for (int gi = threadIdx.x; gi < s.G; gi += kSmallHxThreads) {
             const GroupDesc gd = s.groups[gi];
-            for (int si = gd.sub_begin; si < gd.sub_end; ++si) sgrp[si] = gi;
+            if (gd.x == 0) {   // one group at most
+                diag[0] = gd.sub_begin;
+                diag[1] = gd.sub_end;
+            }
+            // (bits beyond n occur in no string; a flip of one leads out of the sector)
+            const uint32_t x = gd.x >= (1u << sp.n) ? 0x8000u : gd.x;
+            for (int si = gd.sub_begin; si < gd.sub_end; ++si) {
+                terms[si].xw = x;
+                terms[si].pos = gd.pos;
+            }
         }
         __syncthreads();
-        // thread (slice q, string r) takes subgroups q, q + sl, q + 2 sl, ...
+        for (int si = threadIdx.x; si < s.nsub; si += kSmallHxThreads) {
+            const SubDesc sub = s.subs[si];
+            terms[si].xw |= (uint32_t(sub.w) & 0x7fffu) << 16;
+            terms[si].tab = int32_t(sub.tab);
+        }
+        const int d0 = diag[0], d1 = diag[1];
+        __syncthreads();
+        // thread (slice q, string r) takes every sl-th term from the q-th on
         const int sl = small_slices(nsec);
         for (int i = threadIdx.x; i < sl * nsec; i += kSmallHxThreads) {
             const int r = i % nsec, q = i / nsec;
             const uint32_t b = str[r];
+            double dd = 0.0;
+#pragma unroll 4
+            for (int si = d0 + q; si < d1; si += sl) {
+                const SmallTerm m = terms[si];
+                const double t = tabs[m.tab + ((m.pos & 7u) ? pext_pos(b, m.pos) : 0u)];
+                dd += (__popc(b & (m.xw >> 16)) & 1) ? -t : t;
+            }
             V acc = vzero<V>();
-            for (int si = q; si < s.nsub; si += sl) {
-                const GroupDesc gd = groups[sgrp[si]];
-                const uint32_t p = b ^ gd.x;
-                if (p >= (1u << sp.n)) continue;
-                const int rp = rank[p];
-                if (rp < 0) continue;
-                const SubDesc sub = subs[si];
-                const double t = tabs[sub.tab + pext_pos(b, gd.pos)];
-                const double d = (__popc(b & sub.w) & 1) ? -t : t;
-                axpy(acc, d, psi[rp]);
+            axpy(acc, dd, psi[r]);
+            const int nt = s.nsub - (d1 - d0);
+#pragma unroll 2
+            for (int k = q; k < nt; k += sl) {
+                const SmallTerm m = terms[k < d0 ? k : k + (d1 - d0)];
+                const uint32_t x = m.xw & 0xffffu;
+                const int rp = x & 0x8000u ? -1 : int(rank[(b ^ x) & ((1u << sp.n) - 1u)]);
+                const uint32_t u = (m.pos & 7u) == 2u
+                                       ? ((b >> ((m.pos >> 3) & 31u)) & 1u) | ((b >> ((m.pos >> 8) & 31u)) & 1u) << 1
+                                       : pext_pos(b, m.pos);
+                const double t = tabs[m.tab + u];
+                const double d = rp < 0 ? 0.0 : (__popc(b & (m.xw >> 16)) & 1) ? -t : t;
+                axpy(acc, d, psi[max(rp, 0)]);
             }
             if (sl > 1) {
                 part[size_t(q) * nsec + r] = acc;
@@ -255,7 +326,7 @@ __global__ void __launch_bounds__(kSmallHxThreads) k_small_hx(const StateDesc* _
 // Reverse sweep: per gate (last first) each wave's part of Re <lambda|A_j phi>
 // into LDS, then U_j^dag on phi and lambda in the same pass; the per-gate sums
 // (waves added in fixed order) into out_g at the end.
-template <typename V>
+template <typename V, int KT>
 __global__ void __launch_bounds__(kSmallThreads) k_small_adj(const StateDesc* __restrict__ sd, SmallSpace sp) {
     constexpr int kWaves = kSmallThreads / 64;
     extern __shared__ __align__(16) unsigned char smem[];
@@ -276,30 +347,43 @@ __global__ void __launch_bounds__(kSmallThreads) k_small_adj(const StateDesc* __
         gs[j] = SmallGate{g.x, g.pd, g.chain, float(g.csign), cs.x, cs.y};
     }
     __syncthreads();
-    const int w = threadIdx.x >> 6;
-    for (int j = s.M - 1; j >= 0; --j) {
-        const SmallGate g = gs[j];
-        double acc = 0.0;
-        for (int t = threadIdx.x; t < sp.nsec; t += kSmallThreads) {
-            const uint32_t d = str[t];
-            if ((d & g.x) != g.pd) continue;
-            const int re = rank[d ^ g.x];
-            const double sg = double(g.csign) * parity_sign(d & g.chain);
-            V fD = psi[t], fE = psi[re], lD = lam[t], lE = lam[re];
-            // A|D> = s|E>, A|E> = -s|D>: <lam|A phi> = s (lam_E^* phi_D - lam_D^* phi_E)
-            acc += sg * (redot(lE, fD) - redot(lD, fE));
-            const double ss = -sg * g.s;   // U^dag: rotation by -theta
-            givens(fD, fE, g.c, ss);
-            givens(lD, lE, g.c, ss);
-            psi[t] = fD;
-            psi[re] = fE;
-            lam[t] = lD;
-            lam[re] = lE;
-        }
-        acc = wave_total(acc);
-        if ((threadIdx.x & 63) == 0) part[size_t(j) * kWaves + w] = acc;
-        __syncthreads();
+    uint32_t mine[KT];
+    small_strings<KT>(str, sp.nsec, mine);
+    SmallPairs<KT> cur, next;
+    if (s.M > 0) cur.find(gs[s.M - 1], mine, rank);
+    for (int t0 = 0; t0 < s.M; t0 += 8) {   // the wave totals of eight gates at once
+        double acc[8];
+        unroll_n<8>([&](auto uu) {
+            constexpr int u = decltype(uu)::value;
+            const int j = s.M - 1 - t0 - u;
+            acc[u] = 0.0;
+            if (j < 0) return;
+            next.find(gs[max(j - 1, 0)], mine, rank);
+#pragma unroll
+            for (int k = 0; k < KT; ++k) {
+                const int t = int(threadIdx.x) + k * kSmallThreads, re = cur.re[k];
+                if (re >= 0) {
+                    V fD = psi[t], fE = psi[re], lD = lam[t], lE = lam[re];
+                    // A|D> = s|E>, A|E> = -s|D>: <lam|A phi> = s (lam_E^* phi_D - lam_D^* phi_E)
+                    const double v = redot(lE, fD) - redot(lD, fE);
+                    acc[u] += cur.neg[k] ? -v : v;
+                    const double ss = cur.neg[k] ? cur.s : -cur.s;   // U^dag: rotation by -theta
+                    givens(fD, fE, cur.c, ss);
+                    givens(lD, lE, cur.c, ss);
+                    psi[t] = fD;
+                    psi[re] = fE;
+                    lam[t] = lD;
+                    lam[re] = lE;
+                }
+            }
+            __syncthreads();
+            cur = next;
+        });
+        const double tot = wave_totals8(acc, threadIdx.x & 63);
+        const int j = s.M - 1 - t0 - int((threadIdx.x & 63) >> 3);
+        if ((threadIdx.x & 7) == 0 && j >= 0) part[size_t(j) * kWaves + (threadIdx.x >> 6)] = tot;
     }
+    __syncthreads();
     for (int j = threadIdx.x; j < s.M; j += kSmallThreads) {
         double r = 0.0;
 #pragma unroll
@@ -325,27 +409,42 @@ int small_prepare(const SmallSpace& sp) {
     static std::once_flag once;
     static int rc = 0;
     std::call_once(once, [] {
-        const void* fs[6] = {reinterpret_cast<const void*>(&k_small_fwd<double2>),
-                             reinterpret_cast<const void*>(&k_small_hx<double2>),
-                             reinterpret_cast<const void*>(&k_small_adj<double2>),
-                             reinterpret_cast<const void*>(&k_small_fwd<double>),
-                             reinterpret_cast<const void*>(&k_small_hx<double>),
-                             reinterpret_cast<const void*>(&k_small_adj<double>)};
+#define VQE_SMALL_FNS(V)                                                                                             \
+    reinterpret_cast<const void*>(&k_small_hx<V>), reinterpret_cast<const void*>(&k_small_fwd<V, 1>),               \
+        reinterpret_cast<const void*>(&k_small_fwd<V, 2>), reinterpret_cast<const void*>(&k_small_fwd<V, 4>),       \
+        reinterpret_cast<const void*>(&k_small_fwd<V, 8>), reinterpret_cast<const void*>(&k_small_adj<V, 1>),       \
+        reinterpret_cast<const void*>(&k_small_adj<V, 2>), reinterpret_cast<const void*>(&k_small_adj<V, 4>),       \
+        reinterpret_cast<const void*>(&k_small_adj<V, 8>)
+        const void* fs[] = {VQE_SMALL_FNS(double2), VQE_SMALL_FNS(double)};
+#undef VQE_SMALL_FNS
         for (const void* f : fs)
             if (hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, int(kMax)) != hipSuccess) rc = 1;
     });
     return rc;
 }
 
-template <typename V>
-static void launch_small_t(int phase, const StateDesc* sd, int count, const SmallSpace& sp, hipStream_t st) {
+template <typename V, int KT>
+static void launch_small_gates(int phase, const StateDesc* sd, int count, const SmallSpace& sp, hipStream_t st) {
     const size_t lds = small_lds(sp, phase);
     if (phase == kSmallFwd)
-        hipLaunchKernelGGL(k_small_fwd<V>, dim3(1, count), dim3(kSmallThreads), lds, st, sd, sp);
-    else if (phase == kSmallHx)
-        hipLaunchKernelGGL(k_small_hx<V>, dim3(1, count), dim3(kSmallHxThreads), lds, st, sd, sp);
+        hipLaunchKernelGGL((k_small_fwd<V, KT>), dim3(1, count), dim3(kSmallThreads), lds, st, sd, sp);
     else
-        hipLaunchKernelGGL(k_small_adj<V>, dim3(1, count), dim3(kSmallThreads), lds, st, sd, sp);
+        hipLaunchKernelGGL((k_small_adj<V, KT>), dim3(1, count), dim3(kSmallThreads), lds, st, sd, sp);
+}
+
+template <typename V>
+static void launch_small_t(int phase, const StateDesc* sd, int count, const SmallSpace& sp, hipStream_t st) {
+    static_assert(kSmallMaxSector <= 8 * kSmallThreads, "strings per thread");
+    if (phase == kSmallHx)
+        hipLaunchKernelGGL(k_small_hx<V>, dim3(1, count), dim3(kSmallHxThreads), small_lds(sp, phase), st, sd, sp);
+    else if (sp.nsec <= kSmallThreads)
+        launch_small_gates<V, 1>(phase, sd, count, sp, st);
+    else if (sp.nsec <= 2 * kSmallThreads)
+        launch_small_gates<V, 2>(phase, sd, count, sp, st);
+    else if (sp.nsec <= 4 * kSmallThreads)
+        launch_small_gates<V, 4>(phase, sd, count, sp, st);
+    else
+        launch_small_gates<V, 8>(phase, sd, count, sp, st);
 }
 
 void launch_small(int phase, const StateDesc* sd, int count, const SmallSpace& sp, hipStream_t st) {
