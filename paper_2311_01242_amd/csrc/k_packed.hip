@@ -348,17 +348,44 @@ __global__ void __launch_bounds__(BS) k_ppool(const StateDesc* __restrict__ sd,
     const PackedGate* pg = pg_all + run.g0;
     const int2 lc = ldc(run.info + cls);
     const int stride = lc.y & 0xffff;
+    // a gate's parameters and first kPoolAhead x 64 entries are loaded while the
+    // wave's gate before it is summed: a round trip for each was what the sweep
+    // took (875 operators on 20 qubits 49.8 us, so and with as much LDS as the
+    // amplitudes take 34.5; 512 threads 38.1, 1,024 58.3)
+    constexpr int kPoolAhead = 4;
+    struct Gate {
+        double csign;
+        uint32_t chhi, e[kPoolAhead];
+    };
+    auto load = [&](int jl, Gate& g) {
+        const int j = min(jl, ng - 1);
+        const PackedGate q = ldc(pg + j);
+        g.csign = q.csign;
+        g.chhi = q.chhi;
+        const uint32_t* lst = run.ent + lc.x + size_t(j) * stride;
+#pragma unroll
+        for (int u = 0; u < kPoolAhead; ++u) g.e[u] = lane + 64 * u < stride ? ldg32(lst + lane + 64 * u) : run.idle;
+    };
+    Gate cur, next;
+    load(w, next);
     for (int jl = w; jl < ng; jl += BS / 64) {
-        const uint32_t* lst = run.ent + lc.x + size_t(jl) * stride;
-        const PackedGate g = ldc(pg + jl);
-        const double sgn_hi = g.csign * parity_sign(hb0 & g.chhi);
+        cur = next;
+        load(jl + BS / 64, next);
+        const double sgn_hi = cur.csign * parity_sign(hb0 & cur.chhi);
         double acc = 0.0;
-        for (int i = lane; i < stride; i += 64) {
-            const uint32_t e = ldg32(lst + i);
-            if (e == run.idle) break;
+        auto pair = [&](uint32_t e) {
             const int k = pair_first(e), ie = pair_second(e);
             const V fD = shp[k], fE = shp[ie], lD = shl[k], lE = shl[ie];
             acc += sgn_hi * (redot(lE, fD) - redot(lD, fE));
+        };
+#pragma unroll
+        for (int u = 0; u < kPoolAhead; ++u)
+            if (cur.e[u] != run.idle) pair(cur.e[u]);
+        const uint32_t* lst = run.ent + lc.x + size_t(jl) * stride;
+        for (int i = lane + 64 * kPoolAhead; i < stride; i += 64) {
+            const uint32_t e = ldg32(lst + i);
+            if (e == run.idle) break;
+            pair(e);
         }
         acc = wave_total(acc);
         if (lane == 0) s.part_g[size_t(run.g0 + jl) * s.gstride + o] = acc;
@@ -433,7 +460,7 @@ using PoolLauncher = void (*)(const StateDesc*, int, const PoolSweep&, const HxT
 template <int BS, int EPT, typename V>
 static void launch_pool_one(const StateDesc* sd, int count, const PoolSweep& ps,
                             const HxTables* tabs, const int32_t* base, hipStream_t st) {
-    hipLaunchKernelGGL((k_ppool<BS, EPT, V>), dim3(ps.nblk, count), dim3(BS), ps.lds, st, sd, ps.runs,
+    hipLaunchKernelGGL((k_ppool<BS, EPT, V>), dim3(ps.nblk, count), dim3(BS), ps.lds / sizeof(double2) * sizeof(V), st, sd, ps.runs,
                        ps.blk_run, ps.blk0, ps.gates, tabs, base);
 }
 
