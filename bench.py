@@ -182,10 +182,12 @@ def amp_dtype(real):
 
 # phase -> (kernel, source file, bound)
 PHASE_KERNELS = {
-    "forward": ("k_prun<1,*,*> (packed forward gate runs)", "k_packed.hip", "hbm"),
-    "h_apply": ("k_hx_ci<*,*> (string-product sector H-apply, with the two order conversions)",
-                "k_hx_ci.hip", "alu"),
-    "adjoint": ("k_prun<2,*,*> (packed reverse-sweep gate runs)", "k_packed.hip", "hbm"),
+    "forward": ("k_prun<1,*,*> (packed forward gate runs; k_whole_fwd for sectors of one workgroup)",
+                "k_packed.hip", "hbm"),
+    "h_apply": ("k_hx_same + k_hx_cross (string-product sector H-apply as FP64 matrix products; k_hx_ci for small "
+                "sectors and Hamiltonians without that form; with the order conversions)", "k_hx_mm.hip", "alu"),
+    "adjoint": ("k_prun<2,*,*> (packed reverse-sweep gate runs; k_whole_adj for sectors of one workgroup)",
+                "k_packed.hip", "hbm"),
 }
 
 
@@ -201,8 +203,9 @@ def _binom(n, k):
 
 
 def walk_lds_bytes(n, ne, vbytes):
-    """LDS bytes the string-product H-apply's beta-pair walk gathers for one
-    (n, n_e) state: for every row (alpha string), every alpha orbital pair
+    """LDS bytes the walking form of the string-product H-apply (sectors below
+    256 strings, Hamiltonians without the matrix form) gathers in its beta-pair
+    walk for one (n, n_e) state: for every row (alpha string), every alpha orbital pair
     with one orbital occupied in it (a pair class, present for every pair in
     a molecular Hamiltonian), every column (beta string) and every beta pair
     with one orbital occupied in the column (a list entry), one 8-byte pair
@@ -352,11 +355,6 @@ def roofline(b, theta, reps, Hs, nes, kernels=None, pairs=None, traffic_key=None
         recs["forward"]["lds_bytes_per_eval"] = 4 * vbytes * w[1] + w[0]
         recs["adjoint"]["lds_bytes_per_eval"] = 8 * vbytes * w[1] + w[2]
         recs["forward"]["pair_updates_per_eval"] = recs["adjoint"]["pair_updates_per_eval"] = w[1]
-        # string-product H-apply (n <= 26, at most 1024 beta strings): the
-        # beta-pair walk's LDS gathers, the bulk of its LDS traffic
-        if all(H.info()[0] <= 26 and _binom(H.info()[0] // 2, ne // 2) <= 1024 for H, ne in zip(Hs, nes)):
-            recs["h_apply"]["lds_bytes_per_eval"] = sum(walk_lds_bytes(H.info()[0], ne, vbytes)
-                                                        for H, ne in zip(Hs, nes))
     dom = max(recs, key=lambda k: recs[k]["phase_ms"])
     out = dict(recs[dom])
     out["dominant_phase"] = dom
@@ -726,7 +724,7 @@ def run_mlp16(args):
         "higher_is_better": True, "scaling": "weak", "vs_baseline": None, "dtype": "bf16 (products) / fp32",
         "data": "synthetic",
         "config": {"workload": "warm-start MLP 37-256-256-360 trained on 160 samples (16-qubit shapes)"},
-        "roofline": {"bound": "mfma", "kernel": "k_gemm_bf16 (v_mfma_f32_16x16x32_bf16)",
+        "roofline": {"bound": "mfma", "kernel": "k_mlp_fwd + k_mlp_back (v_mfma_f32_16x16x32_bf16)",
                      "achieved": round(achieved, 3), "peak": BF16_PEAK_TFLOPS, "unit": "TFLOP/s",
                      "frac": round(achieved / BF16_PEAK_TFLOPS, 6), "traffic": None,
                      "algorithmic_flops_per_step": flops},

@@ -17,8 +17,9 @@ Three sub-commands, both reading the CSV files rocprofv3 writes with
             phase, with the sha256 of the kernel source it was measured on)
             and prints a markdown table.
 
-Phase of a kernel: k_prun<1,...> / k_run_fwd / k_small_fwd forward,
-k_prun<2,...> / k_run_adj / k_small_adj adjoint, k_ppool pool sweep, k_hx_ci /
+Phase of a kernel: k_prun<1,...> / k_whole_fwd / k_run_fwd / k_small_fwd
+forward, k_prun<2,...> / k_whole_adj / k_run_adj / k_small_adj adjoint, k_ppool
+pool sweep, k_hx_same / k_hx_cross / k_hx_ci /
 k_ci_scatter / k_ci_gather / k_hx_packed / k_hx_sector / k_hx_dense /
 k_small_hx H-apply.
 """
@@ -33,20 +34,20 @@ import os
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_2311_01242_amd", "csrc")
-PHASE_SOURCE = {"forward": "k_packed.hip", "adjoint": "k_packed.hip", "h_apply": "k_hx_ci.hip"}
+PHASE_SOURCE = {"forward": "k_packed.hip", "adjoint": "k_packed.hip", "h_apply": "k_hx_mm.hip"}
 COPY_BYTES = 2 ** 31
 
 
 def phase_of(name: str):
-    if "k_prun<1" in name or "k_run_fwd" in name or "k_small_fwd" in name:
+    if "k_prun<1" in name or "k_whole_fwd" in name or "k_run_fwd" in name or "k_small_fwd" in name:
         return "forward"
-    if "k_prun<2" in name or "k_run_adj" in name or "k_small_adj" in name:
+    if "k_prun<2" in name or "k_whole_adj" in name or "k_run_adj" in name or "k_small_adj" in name:
         return "adjoint"
     if "k_small_hx" in name:
         return "h_apply"
     if "k_ppool" in name:
         return "pool_sweep"
-    if any(k in name for k in ("k_hx_ci", "k_ci_scatter", "k_ci_gather", "k_hx_packed",
+    if any(k in name for k in ("k_hx_ci", "k_hx_same", "k_hx_cross", "k_ci_scatter", "k_ci_gather", "k_hx_packed",
                                "k_hx_sector", "k_hx_dense")):
         return "h_apply"
     return None
@@ -80,14 +81,15 @@ def cmd_stats(args):
 
 def _sum_counter(path):
     """Counter totals per phase, and the phase's launches: for the H-apply only
-    the k_hx_* kernels count (the order conversions' bytes are charged to
-    them, as bench.py's phase time includes them)."""
+    the k_hx_* kernels count, the two of the matrix form as one (the order
+    conversions' bytes are charged to them, as bench.py's phase time includes
+    them)."""
     tot = collections.defaultdict(float)
     cnt = collections.Counter()
     for r in csv.DictReader(open(path)):
         ph = phase_of(r["Kernel_Name"]) or short(r["Kernel_Name"])
         tot[ph] += float(r["Counter_Value"])
-        if ph != "h_apply" or "k_hx_" in r["Kernel_Name"]:
+        if ph != "h_apply" or ("k_hx_" in r["Kernel_Name"] and "k_hx_same" not in r["Kernel_Name"]):
             cnt[ph] += 1
     return tot, cnt
 
