@@ -282,7 +282,7 @@ struct WholePlan {
 };
 
 struct DevAnsatz {
-    std::map<std::pair<const CiSpace*, int>, WholePlan*> whole;   // by string space and signed amplitudes
+    std::map<std::pair<const CiSpace*, int>, WholePlan*> whole;   // by string space and form
     GateDesc* gates = nullptr;
     std::map<std::pair<int64_t, int64_t>, AnsatzPlan*> plans;
     std::map<std::tuple<int, int, int, int, bool>, PackedPlan*> packed;   // by (L, fwd, adj threads, tile cap, ordered)
@@ -1925,117 +1925,131 @@ static void whole_pairs(const GateDesc& g, const CiSpace& cs, bool sgn, std::vec
     }
 }
 
-static int whole_plan(const vqe_ansatz* A, DevAnsatz* da, const CiSpace& cs, uint32_t ref, bool sgn,
+// form: kWholeFit, whether the state fits, the threads and the pairs (asked
+// for first); kWholePlain and kWholeSigned, the lists for the amplitudes' signs.
+enum WholeForm { kWholePlain = 0, kWholeSigned = 1, kWholeFit = 2 };
+static int whole_plan(const vqe_ansatz* A, DevAnsatz* da, const CiSpace& cs, uint32_t ref, WholeForm form,
                       const WholePlan** out) {
     std::lock_guard<std::mutex> lk(A->mu);
-    const auto key = std::make_pair(&cs, sgn ? 1 : 0);
+    const auto key = std::make_pair(&cs, int(form));
     auto it = da->whole.find(key);
     if (it != da->whole.end()) {
         *out = it->second;
         return VQE_OK;
     }
     const size_t M = A->gates.size();
-    std::vector<int> cnt(M);
     std::vector<SpinPair> rows, cols;
-    for (size_t j = 0; j < M; ++j) {
-        whole_pairs(A->gates[j], cs, false, &rows, &cols);
-        cnt[j] = int(rows.size() * cols.size());
+    if (form == kWholeFit) {
+        std::vector<int> cnt(M);
+        auto* p = new WholePlan();
+        for (size_t j = 0; j < M; ++j) {
+            whole_pairs(A->gates[j], cs, false, &rows, &cols);
+            cnt[j] = int(rows.size() * cols.size());
+            p->pairs += cnt[j];
+        }
+        int threads = 0;
+        if (whole_prepare(cs.NA * cs.NB, int(M), cnt.data(), &threads) == 0) p->args.threads = threads;
+        da->whole[key] = p;
+        *out = p;
+        return VQE_OK;
     }
+    const bool sgn = form == kWholeSigned;
+    const auto fit_it = da->whole.find(std::make_pair(&cs, int(kWholeFit)));
+    if (fit_it == da->whole.end()) return fail(VQE_EINVAL, "whole-state plan before its fit");
+    const WholePlan* fit = fit_it->second;
     auto* p = new WholePlan();
-    for (int c : cnt) p->pairs += c;
+    p->pairs = fit->pairs;
     WholeArgs& w = p->args;
     w.nE = cs.NA * cs.NB;
     w.M = int32_t(M);
-    int threads = 0;
-    if (whole_prepare(w.nE, w.M, cnt.data(), &threads) == 0) {
-        const int nw = threads / 64;
-        std::vector<std::vector<uint32_t>> lists(M);
-        for (size_t j = 0; j < M; ++j) {
-            whole_pairs(A->gates[j], cs, sgn, &rows, &cols);
-            const int neg = A->gates[j].csign < 0.0 ? 1 : 0;
-            lists[j].reserve(size_t(cnt[j]));
-            for (const SpinPair& r : rows)
-                for (const SpinPair& c : cols) {
-                    const uint32_t d = uint32_t(r.d * cs.NB + c.d), e = uint32_t(r.e * cs.NB + c.e);
-                    lists[j].push_back((r.par + c.par + neg) & 1 ? e | d << 16 : d | e << 16);
-                }
-        }
-        WaveSplit split;
-        std::vector<uint16_t> sa(cs.sa.begin(), cs.sa.end()), sb(cs.sb.begin(), cs.sb.end());
-        split.low = cs.oa + cs.ob;
-        split.blocks.push_back({0u, sa.data(), sb.data(), cs.NA, cs.NB});
-        std::vector<char> cut;
-        if (nw < kWholeWaves) wave_cuts(A->gates.data(), M, lists.data(), nw, &split, &cut);
-        else cut.assign(M, 1);
-        // a gate's passes: the most of a wave
-        std::vector<int> passes(M);
-        auto stretches = [&](auto&& f) {
-            for (size_t j = 0; j < M;) {
-                size_t j2 = j + 1;
-                while (j2 < M && !cut[j2 - 1]) ++j2;
-                split.set(&A->gates[j], &lists[j], j2 - j, nw);
-                for (; j < j2; ++j) f(j);
+    const int threads = fit->args.threads;
+    const int nw = threads / 64;
+    std::vector<std::vector<uint32_t>> lists(M);
+    for (size_t j = 0; j < M; ++j) {
+        whole_pairs(A->gates[j], cs, sgn, &rows, &cols);
+        const int neg = A->gates[j].csign < 0.0 ? 1 : 0;
+        lists[j].reserve(rows.size() * cols.size());
+        for (const SpinPair& r : rows)
+            for (const SpinPair& c : cols) {
+                const uint32_t d = uint32_t(r.d * cs.NB + c.d), e = uint32_t(r.e * cs.NB + c.e);
+                lists[j].push_back((r.par + c.par + neg) & 1 ? e | d << 16 : d | e << 16);
             }
-        };
-        std::vector<uint32_t> ent;
-        std::vector<size_t> at(M);
-        const uint32_t idle = uint32_t(w.nE) | uint32_t(w.nE + 1) << 16;
-        stretches([&](size_t j) {   // placed apart, then moved to their segments' rows
-            uint32_t c[16];
-            split.count(lists[j], c);
-            passes[j] = std::max(1, int((*std::max_element(c, c + nw) + 63) / 64));
-            at[j] = ent.size();
-            ent.resize(ent.size() + size_t(passes[j]) * size_t(threads), idle);
-            split.place(lists[j], ent.data() + at[j], 0);
-        });
-        const size_t ahead = size_t(kListAhead) * size_t(kWholePlaces) * size_t(threads);
-        std::vector<uint32_t> laid;
-        laid.reserve(ent.size() + ahead);
-        std::vector<WholeSeg> seg;
-        for (int& x : passes)   // places: 1, 2 or 4 where the kernel has a loop for them
-            if (x == 3 && threads <= 256) x = 4;
-        for (size_t j = 0; j < M;) {
-            // gates of as many places, and short stretches of fewer between them
-            constexpr size_t kShort = 16;
-            const int most = passes[j];
-            size_t j2 = j + 1, end = j + 1;
-            while (j2 < M && passes[j2] <= most && j2 - end < kShort)
-                if (passes[j2++] == most) end = j2;
-            if (j2 == M && j2 - end < kShort) end = M;
-            seg.push_back(WholeSeg{int32_t(j), int32_t(end), most, int32_t(laid.size())});
-            for (; j < end; ++j) {
-                const auto from = ent.begin() + ptrdiff_t(at[j]);
-                const size_t have = std::min(size_t(most) * size_t(threads), (j + 1 < M ? at[j + 1] : ent.size()) - at[j]);
-                laid.insert(laid.end(), from, from + ptrdiff_t(have));
-                laid.insert(laid.end(), size_t(most) * size_t(threads) - have, idle);
-            }
-        }
-        laid.insert(laid.end(), ahead, idle);
-        std::vector<uint32_t> meet((M + 8 + 31) / 32 + 2, 0u);
-        for (size_t j = 0; j + 1 < M; ++j)
-            if (cut[j]) meet[(j + 8) / 32] |= 1u << ((j + 8) % 32);
-        const uint32_t ra = compact_even_host(ref), rb = compact_even_host(ref >> 1);
-        w.ref = cs.rank_a[ra] * cs.NB + cs.rank_b[rb];
-        int cross = 0;   // alpha orbitals after a beta one
-        for (uint32_t m = rb; sgn && m; m &= m - 1)
-            cross += __builtin_popcount(ra & ~((2u << __builtin_ctz(m)) - 1u));
-        w.ref_neg = cross & 1;
-        int rc = upload(&p->d_ent, laid.data(), laid.size(), ahead);
-        if (!rc) rc = upload(&p->d_seg, seg.data(), seg.size());
-        if (!rc) rc = upload(&p->d_meet, meet.data(), meet.size());
-        if (rc) {
-            (void)hipFree(p->d_ent);
-            (void)hipFree(p->d_seg);
-            (void)hipFree(p->d_meet);
-            delete p;
-            return rc;
-        }
-        w.ent = p->d_ent + ahead;
-        w.seg = p->d_seg;
-        w.meet = p->d_meet;
-        w.nseg = int32_t(seg.size());
-        w.threads = threads;
     }
+    WaveSplit split;
+    std::vector<uint16_t> sa(cs.sa.begin(), cs.sa.end()), sb(cs.sb.begin(), cs.sb.end());
+    split.low = cs.oa + cs.ob;
+    split.blocks.push_back({0u, sa.data(), sb.data(), cs.NA, cs.NB});
+    std::vector<char> cut;
+    if (nw < kWholeWaves) wave_cuts(A->gates.data(), M, lists.data(), nw, &split, &cut);
+    else cut.assign(M, 1);
+    // a gate's passes: the most of a wave
+    std::vector<int> passes(M);
+    auto stretches = [&](auto&& f) {
+        for (size_t j = 0; j < M;) {
+            size_t j2 = j + 1;
+            while (j2 < M && !cut[j2 - 1]) ++j2;
+            split.set(&A->gates[j], &lists[j], j2 - j, nw);
+            for (; j < j2; ++j) f(j);
+        }
+    };
+    std::vector<uint32_t> ent;
+    std::vector<size_t> at(M);
+    const uint32_t idle = uint32_t(w.nE) | uint32_t(w.nE + 1) << 16;
+    stretches([&](size_t j) {   // placed apart, then moved to their segments' rows
+        uint32_t c[16];
+        split.count(lists[j], c);
+        passes[j] = std::max(1, int((*std::max_element(c, c + nw) + 63) / 64));
+        at[j] = ent.size();
+        ent.resize(ent.size() + size_t(passes[j]) * size_t(threads), idle);
+        split.place(lists[j], ent.data() + at[j], 0);
+    });
+    const size_t ahead = size_t(kListAhead) * size_t(kWholePlaces) * size_t(threads);
+    std::vector<uint32_t> laid;
+    laid.reserve(ent.size() + ahead);
+    std::vector<WholeSeg> seg;
+    for (int& x : passes)   // places: 1, 2 or 4 where the kernel has a loop for them
+        if (x == 3 && threads <= 256) x = 4;
+    for (size_t j = 0; j < M;) {
+        // gates of as many places, and short stretches of fewer between them
+        constexpr size_t kShort = 16;
+        const int most = passes[j];
+        size_t j2 = j + 1, end = j + 1;
+        while (j2 < M && passes[j2] <= most && j2 - end < kShort)
+            if (passes[j2++] == most) end = j2;
+        if (j2 == M && j2 - end < kShort) end = M;
+        seg.push_back(WholeSeg{int32_t(j), int32_t(end), most, int32_t(laid.size())});
+        for (; j < end; ++j) {
+            const auto from = ent.begin() + ptrdiff_t(at[j]);
+            const size_t have = std::min(size_t(most) * size_t(threads), (j + 1 < M ? at[j + 1] : ent.size()) - at[j]);
+            laid.insert(laid.end(), from, from + ptrdiff_t(have));
+            laid.insert(laid.end(), size_t(most) * size_t(threads) - have, idle);
+        }
+    }
+    laid.insert(laid.end(), ahead, idle);
+    std::vector<uint32_t> meet((M + 8 + 31) / 32 + 2, 0u);
+    for (size_t j = 0; j + 1 < M; ++j)
+        if (cut[j]) meet[(j + 8) / 32] |= 1u << ((j + 8) % 32);
+    const uint32_t ra = compact_even_host(ref), rb = compact_even_host(ref >> 1);
+    w.ref = cs.rank_a[ra] * cs.NB + cs.rank_b[rb];
+    int cross = 0;   // alpha orbitals after a beta one
+    for (uint32_t m = rb; sgn && m; m &= m - 1)
+        cross += __builtin_popcount(ra & ~((2u << __builtin_ctz(m)) - 1u));
+    w.ref_neg = cross & 1;
+    int rc = upload(&p->d_ent, laid.data(), laid.size(), ahead);
+    if (!rc) rc = upload(&p->d_seg, seg.data(), seg.size());
+    if (!rc) rc = upload(&p->d_meet, meet.data(), meet.size());
+    if (rc) {
+        (void)hipFree(p->d_ent);
+        (void)hipFree(p->d_seg);
+        (void)hipFree(p->d_meet);
+        delete p;
+        return rc;
+    }
+    w.ent = p->d_ent + ahead;
+    w.seg = p->d_seg;
+    w.meet = p->d_meet;
+    w.nseg = int32_t(seg.size());
+    w.threads = threads;
     da->whole[key] = p;
     *out = p;
     return VQE_OK;
@@ -2975,7 +2989,7 @@ static int make_eval_plan(const vqe_ansatz* A, int ne, bool batched, EvalPlan* e
             if (cs && cs->NB <= kCiMaxCols) {
                 args = cs->args();
                 args.nsplit = batched ? 1 : ci_choose_splits(args);
-                if (int rc = whole_plan(A, da, *cs, uint32_t((uint64_t(1) << ne) - 1), false, &ep->whole)) return rc;
+                if (int rc = whole_plan(A, da, *cs, uint32_t((uint64_t(1) << ne) - 1), kWholeFit, &ep->whole)) return rc;
                 if (ep->whole->args.threads == 0 || ci_prepare(args) != 0) ep->whole = nullptr;
             }
             if (ep->whole) {
@@ -3613,16 +3627,21 @@ static int mm_choose(const vqe_hamiltonian* H, DevHam* dh, const EvalPlan& ep, b
     *yes = m != nullptr;
     return VQE_OK;
 }
-static int mm_use(EvalPlan* ep) {
-    ep->mm = true;
-    ep->ciargs.nsplit = 1;
-    ep->nblk_e = ep->cspace->NA;
-    if (ep->whole) {   // the passes on signed amplitudes
+// The rest of the plan, once it is known whether the H-apply takes its matrix
+// form (then on signed amplitudes).
+static int form_use(EvalPlan* ep, bool mm) {
+    if (mm) {
+        ep->mm = true;
+        ep->ciargs.nsplit = 1;
+        ep->nblk_e = ep->cspace->NA;
+    }
+    if (ep->whole) {
         DevAnsatz* da;
         if (int rc = dev_ansatz(ep->A, &da)) return rc;
-        return whole_plan(ep->A, da, *ep->cspace, uint32_t((uint64_t(1) << ep->ne) - 1), true, &ep->whole);
+        return whole_plan(ep->A, da, *ep->cspace, uint32_t((uint64_t(1) << ep->ne) - 1),
+                          mm ? kWholeSigned : kWholePlain, &ep->whole);
     }
-    ep->perm = ep->lay->d_perm_s;
+    if (mm) ep->perm = ep->lay->d_perm_s;
     return VQE_OK;
 }
 
@@ -3703,8 +3722,7 @@ int setup_single(const vqe_hamiltonian* H, const vqe_ansatz* A, int ne, const do
     small_fit_ham(&e->ep, H);
     bool mm;
     if (int rc = mm_choose(H, e->dh, e->ep, &mm)) return rc;
-    if (mm)
-        if (int rc = mm_use(&e->ep)) return rc;
+    if (int rc = form_use(&e->ep, mm)) return rc;
     if (int rc = dev_ansatz(A, &e->da)) return rc;
     const EvalPlan& ep = e->ep;
     HxWork* hw = nullptr;
@@ -4571,8 +4589,7 @@ extern "C" int vqe_batch_create(int S, const vqe_hamiltonian* const* H, const vq
             all[size_t(cls[i])] = yes;
         }
         for (size_t c = 0; c < rep.size(); ++c)
-            if (all[c])
-                if (int rc = mm_use(&b->classes[c].ep)) return rc;
+            if (int rc = form_use(&b->classes[c].ep, all[c])) return rc;
     }
     size_t need = 0;
     for (int i = 0; i < S; ++i)
