@@ -8,6 +8,7 @@
 #include <utility>
 
 #include "internal.h"
+#include "run_layout.h"
 
 namespace vqe {
 

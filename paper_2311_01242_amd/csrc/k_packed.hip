@@ -109,7 +109,8 @@ __global__ void __launch_bounds__(BS) k_prun(const StateDesc* __restrict__ sd, P
     // high bits outside the window (the window's part is in each entry);
     // staged once; the first is read by broadcast in the gate loop, the
     // second (reverse sweep) applied to the gate's tile total at the end
-    double2* gpar = sh + (size_t(VEC) * nV * sizeof(V) + 15) / 16;
+    const RunLds lay = tiled_run_lds(VEC, sizeof(V), run.max_entries, ng, BS / 64);
+    double2* gpar = sh + lay.par / 16;
     // the state index of each staged entry, kept for the write-back
     int gix[2 * EPT];
     {   // all loads first (clamped into the tile), then the LDS stores
@@ -225,7 +226,7 @@ __global__ void __launch_bounds__(BS) k_prun(const StateDesc* __restrict__ sd, P
     // one checks each gate.  The reverse sweep takes the wave totals of a
     // round's gates together after them (wave_totals8) into wsum; the waves
     // are added after the last gate.
-    double* wsum = reinterpret_cast<double*>(gpar + 2 * ng);   // [ng][BS / 64], VEC = 2 only
+    double* wsum = reinterpret_cast<double*>(sh + lay.wsum / 16);   // [ng][BS / 64], VEC = 2 only
     auto meets = [&](int t0) -> uint32_t {   // of the gates t0 .. t0 + 7, t0 a multiple of 8
         const uint64_t m = fwd ? (t0 < 64 ? run.meet_fwd[0] : run.meet_fwd[1])
                                : (t0 < 64 ? run.meet_adj[0] : run.meet_adj[1]);
@@ -423,11 +424,7 @@ using PackedLauncher = void (*)(const StateDesc*, int, const PackedRun&, const P
 template <int VEC, int BS, int EPT, typename V>
 static void launch_one(const StateDesc* sd, int count, const PackedRun& run, const PackedGate* pg,
                        hipStream_t st) {
-    // the tile's amplitudes and the idle pair (16-byte aligned), then 2 double2
-    // and the reverse sweep's wave totals per gate
-    const size_t lds = (size_t(run.max_entries + 2) * VEC * sizeof(V) + 15) / 16 * 16 +
-                       2 * size_t(run.g1 - run.g0) * sizeof(double2) +
-                       (VEC == 2 ? size_t(run.g1 - run.g0) * (BS / 64) * sizeof(double) : 0);
+    const size_t lds = tiled_run_lds(VEC, sizeof(V), run.max_entries, run.g1 - run.g0, BS / 64).total;
     const int nx = run.live ? run.nlive : run.ntiles;
     if (nx == 0) return;   // a run with no live tile: nothing to do, no partials
     hipLaunchKernelGGL((k_prun<VEC, BS, EPT, V>), dim3(nx, count), dim3(BS), lds, st, sd, run, pg);

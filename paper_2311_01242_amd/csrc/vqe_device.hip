@@ -2441,7 +2441,7 @@ static int packed_plan(const vqe_ansatz* A, DevAnsatz* da, const PackedLayout& l
             p->gcnt[size_t(k)] = r.ntiles;
         }
         p->gstride = std::max(p->gstride, r.ntiles);
-        p->max_lds = std::max(p->max_lds, (size_t(maxe + 2) * 2 + 2 * size_t(ng)) * sizeof(double2) + size_t(ng) * 16 * sizeof(double));
+        p->max_lds = std::max(p->max_lds, tiled_run_lds(2, sizeof(double2), maxe, int(ng), packed_shape_threads(r.shape_adj) / 64).total);
         p->max_entries = std::max(p->max_entries, maxe);
         p->max_gates = std::max(p->max_gates, int(ng));
         p->run_work.push_back(double(moved_live) * double(ng));
