@@ -212,8 +212,8 @@ __global__ void __launch_bounds__(kSmallThreads) k_small_fwd(const StateDesc* __
 template <typename V>
 __global__ void __launch_bounds__(kSmallHxThreads) k_small_hx(const StateDesc* __restrict__ sd, SmallSpace sp) {
     extern __shared__ __align__(16) unsigned char smem[];
-    __shared__ double red[kSmallHxThreads / 64];
     const SmallLayout L = small_layout(sp, kSmallHx);
+    double* red = reinterpret_cast<double*>(smem + L.total);   // [waves]
     const StateDesc& s = sd[blockIdx.y];
     const int nsec = sp.nsec;
     V* psi = reinterpret_cast<V*>(smem + L.vec);
@@ -394,16 +394,16 @@ __global__ void __launch_bounds__(kSmallThreads) k_small_adj(const StateDesc* __
 
 size_t small_lds(const SmallSpace& sp, int phase) {
     const size_t base = small_layout(sp, phase).total;
+    if (phase == kSmallHx) return base + 8 * size_t(kSmallHxThreads / 64);
     return phase == kSmallAdj ? base + 8 * size_t(kSmallThreads / 64) * size_t(sp.M) : base;
 }
 
-// The launches' LDS (dynamic plus the H-apply's static reduction slots) must
-// fit the CU's 160 KiB; beyond 64 KiB the kernels are allowed the whole of it
-// (once).
+// The launches' LDS must fit the CU's 160 KiB; beyond 64 KiB the kernels are
+// allowed the whole of it (once).  None has static LDS, which would come on top.
 int small_prepare(const SmallSpace& sp) {
     constexpr size_t kMax = size_t(160) << 10;
     size_t lds = 0;
-    for (int ph = 0; ph < 3; ++ph) lds = std::max(lds, small_lds(sp, ph) + 8 * size_t(kSmallHxThreads / 64));
+    for (int ph = 0; ph < 3; ++ph) lds = std::max(lds, small_lds(sp, ph));
     if (lds > kMax) return 1;
     if (lds <= (64u << 10)) return 0;
     static std::once_flag once;
@@ -419,6 +419,7 @@ int small_prepare(const SmallSpace& sp) {
 #undef VQE_SMALL_FNS
         for (const void* f : fs)
             if (hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, int(kMax)) != hipSuccess) rc = 1;
+        if (rc) (void)hipGetLastError();   // not the next launch's
     });
     return rc;
 }

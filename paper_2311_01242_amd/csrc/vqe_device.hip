@@ -3050,27 +3050,29 @@ static int make_eval_plan(const vqe_ansatz* A, int ne, bool batched, EvalPlan* e
             binom(n, __builtin_popcount(ref)) <= kSmallMaxSector && A->gates.size() <= size_t(kSmallMaxGates)) {
             SmallTables* st;
             if (int rc = small_tables(n, __builtin_popcount(ref), &st)) return rc;
-            ep->small = true;
-            ep->sspace.str = st->str;
-            ep->sspace.rank = st->rank;
-            ep->sspace.n = n;
-            ep->sspace.nsec = st->nsec;
-            ep->sspace.ref_rank = st->rank_h[ref];
-            ep->sspace.M = int32_t(A->gates.size());
-            ep->sspace.ham_lds = 0;
+            SmallSpace sp{};
+            sp.str = st->str;
+            sp.rank = st->rank;
+            sp.n = n;
+            sp.nsec = st->nsec;
+            sp.ref_rank = st->rank_h[ref];
+            sp.M = int32_t(A->gates.size());
             // pair moves are real rotations and H is a real matrix (as on the
             // string-product path): real amplitudes unless switched off
-            ep->real = g_real_enabled.load() != 0;
-            ep->sspace.vbytes = ep->real ? 8 : 16;
-            ep->elems = st->nsec;
-            ep->nblk_e = 1;
-            ep->gstride = 1;
-            ep->d_gcnt = nullptr;
-            ep->fwd_bytes = double(ep->sspace.vbytes) * double(st->nsec);        // phi written
-            ep->adj_bytes = 2.0 * double(ep->sspace.vbytes) * double(st->nsec);  // phi, lambda read
-            ep->fwd_steps = ep->adj_steps = 1;
-            if (small_prepare(ep->sspace) != 0)
-                return fail(VQE_EDEVICE, "could not enable the small-sector kernels' LDS size");
+            const bool real = g_real_enabled.load() != 0;
+            sp.vbytes = real ? 8 : 16;
+            if (small_prepare(sp) == 0) {   // (else full vectors)
+                ep->small = true;
+                ep->sspace = sp;
+                ep->real = real;
+                ep->elems = st->nsec;
+                ep->nblk_e = 1;
+                ep->gstride = 1;
+                ep->d_gcnt = nullptr;
+                ep->fwd_bytes = double(sp.vbytes) * double(st->nsec);        // phi written
+                ep->adj_bytes = 2.0 * double(sp.vbytes) * double(st->nsec);  // phi, lambda read
+                ep->fwd_steps = ep->adj_steps = 1;
+            }
         }
     }
     return VQE_OK;
