@@ -4889,7 +4889,8 @@ extern "C" int vqe_set_run_threads(int n_qubits, int batched, int fwd_threads, i
 
 extern "C" int vqe_set_tile_cap(int n_qubits, int batched, int entries) {
     if (n_qubits < 1 || n_qubits > 32) return fail(VQE_ERANGE, "n_qubits must be in [1, 32]");
-    if (entries != 0 && (entries < 16 || entries > kMaxTileEntries))
+    constexpr int kCapMax = 8192;   // (a plan's tiles hold at most kMaxTileEntries)
+    if (entries != 0 && (entries < 16 || entries > kCapMax))
         return fail(VQE_ERANGE, "entries must be 0 or in [16, 8192]");
     std::lock_guard<std::mutex> lk(g_tune_mu);
     if (entries == 0)
