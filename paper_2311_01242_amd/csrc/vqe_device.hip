@@ -20,6 +20,7 @@
 #include <cmath>
 #include <cstring>
 #include <memory>
+#include <set>
 #include <tuple>
 
 #include "device_common.h"
@@ -3619,9 +3620,35 @@ extern "C" int vqe_expectation(const vqe_state* s, const vqe_hamiltonian* H, dou
 // gradient (4 strings) 99 us walking, 110 with it; 20 states of 12 qubits
 // (400 strings each) 170 us walking, 163 with it.
 constexpr int64_t kMmMinSize = 256;
-static int mm_choose(const vqe_hamiltonian* H, DevHam* dh, const EvalPlan& ep, bool* yes) {
+static bool mm_plan(const EvalPlan& ep) { return ep.ci && ep.real && ep.elems >= kMmMinSize; }
+
+// Device memory that H's matrices under plan ep would still take.
+static size_t mm_missing(const vqe_hamiltonian* H, const DevHam* dh, const EvalPlan& ep) {
+    if (!mm_plan(ep) || !ep.cspace->mm_ok) return 0;
+    std::lock_guard<std::mutex> lk(H->mu);
+    if (dh->ci && dh->ci->mm.count(ep.cspace)) return 0;
+    const CiMmArgs& m = ep.cspace->mm;
+    return sizeof(double) * (size_t(m.ng) * size_t(m.m_pad) + size_t(m.na_pad) * size_t(m.na_pad) +
+                             size_t(m.nb_pad) * size_t(m.nb_pad));
+}
+
+// Whether there is memory for `matrices` beside `others` that are yet to be
+// allocated.  The matrices are as large as a third of a state's vectors (24
+// qubits 14 MB and 41 MB): evaluations that fill the device walk instead.  The
+// margin is for what is not counted (pair lists, descriptors).
+static int mm_room(size_t matrices, size_t others, bool* room) {
+    *room = true;
+    if (matrices == 0) return VQE_OK;
+    constexpr size_t kMargin = size_t(256) << 20;
+    size_t fr = 0, tot = 0;
+    HIPCHK(hipMemGetInfo(&fr, &tot));
+    *room = matrices + others + kMargin <= fr;
+    return VQE_OK;
+}
+
+static int mm_choose(const vqe_hamiltonian* H, DevHam* dh, const EvalPlan& ep, bool room, bool* yes) {
     *yes = false;
-    if (!ep.ci || !ep.real || ep.elems < kMmMinSize) return VQE_OK;
+    if (!mm_plan(ep) || (!room && mm_missing(H, dh, ep) > 0)) return VQE_OK;
     CiHam* ch;
     if (int rc = ci_ham(H, dh, &ch)) return rc;
     const CiMatrix* m;
@@ -3722,8 +3749,9 @@ int setup_single(const vqe_hamiltonian* H, const vqe_ansatz* A, int ne, const do
     if (int rc = dev_ham(H, &e->dh)) return rc;
     if (int rc = make_eval_plan(A, ne, false, &e->ep, 0, whole_ok)) return rc;
     small_fit_ham(&e->ep, H);
-    bool mm;
-    if (int rc = mm_choose(H, e->dh, e->ep, &mm)) return rc;
+    bool mm, room;
+    if (int rc = mm_room(mm_missing(H, e->dh, e->ep), 3 * sizeof(double2) * size_t(e->ep.elems), &room)) return rc;
+    if (int rc = mm_choose(H, e->dh, e->ep, room, &mm)) return rc;
     if (int rc = form_use(&e->ep, mm)) return rc;
     if (int rc = dev_ansatz(A, &e->da)) return rc;
     const EvalPlan& ep = e->ep;
@@ -4580,22 +4608,33 @@ extern "C" int vqe_batch_create(int S, const vqe_hamiltonian* const* H, const vq
             }
             persist = persist && b->classes[c].ep.packed && b->classes[c].ep.hx.L == Lp;
         }
+    size_t need = 0;
+    for (int i = 0; i < S; ++i)
+        need += (b->classes[cls[i]].ep.ci ? 3 : 2) * sizeof(double2) * size_t(b->classes[cls[i]].ep.elems);
     {   // the matrix form of the H-apply for classes whose Hamiltonians all have one
+        size_t matrices = 0, parts = 0;
+        std::set<std::pair<const vqe_hamiltonian*, const CiSpace*>> seen;
+        for (int i = 0; i < S; ++i) {
+            const EvalPlan& ep = b->classes[cls[i]].ep;
+            DevHam* dh;
+            if (int rc = dev_ham(H[i], &dh)) return rc;
+            if (seen.insert({H[i], ep.cspace}).second) matrices += mm_missing(H[i], dh, ep);
+            parts += sizeof(double) * size_t(ep.M) * size_t(ep.gstride + 2);
+        }
+        bool room;
+        if (int rc = mm_room(matrices, need + parts, &room)) return rc;
         std::vector<char> all(rep.size(), 1);
         for (int i = 0; i < S; ++i) {
             if (!all[size_t(cls[i])]) continue;
             DevHam* dh;
             if (int rc = dev_ham(H[i], &dh)) return rc;
             bool yes;
-            if (int rc = mm_choose(H[i], dh, b->classes[cls[i]].ep, &yes)) return rc;
+            if (int rc = mm_choose(H[i], dh, b->classes[cls[i]].ep, room, &yes)) return rc;
             all[size_t(cls[i])] = yes;
         }
         for (size_t c = 0; c < rep.size(); ++c)
             if (int rc = form_use(&b->classes[c].ep, all[c])) return rc;
     }
-    size_t need = 0;
-    for (int i = 0; i < S; ++i)
-        need += (b->classes[cls[i]].ep.ci ? 3 : 2) * sizeof(double2) * size_t(b->classes[cls[i]].ep.elems);
     if (int rc = fits_device(need)) return rc;
     if (int rc = dalloc(b, &b->theta_dev, b->poff[S])) return rc;
     if (int rc = dalloc(b, &b->e_dev, S)) return rc;
