@@ -3594,8 +3594,12 @@ extern "C" int vqe_expectation(const vqe_state* s, const vqe_hamiltonian* H, dou
     if (int rc = ham_chunks(H, dh, kDenseL, &hw)) return rc;
     int gx, gy;
     expect_grid(N, hw->count, &gx, &gy);
-    // the index list of the nonzero amplitudes, up to 64 MiB of it
-    const bool listed = s->n <= 24;
+    // the index list of the nonzero amplitudes, up to 64 MiB of it, where the
+    // outputs left out can pay for its three launches (8 us).  Reference state,
+    // listed / all outputs, us: two-body Hamiltonians on 4 qubits 36 / 28, 12 qubits
+    // 47 / 40, 14 qubits 50 / 46, 15 qubits 51 / 71, 16 qubits 52 / 129; 200 diagonal
+    // strings on 15 qubits 43 / 44, 16 qubits 43 / 60
+    const bool listed = s->n <= 24 && double(N) * (double(H->c.size()) + 2000.0) > 1e8;
     StateCall c;
     if (int rc = begin_state_call(s, 0, 0, gx * gy, &c, listed ? N + nz_counts(N) : 0)) return rc;
     c.sd.chunks = hw->chunks;
