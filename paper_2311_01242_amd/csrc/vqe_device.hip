@@ -2815,6 +2815,22 @@ static int workspace(void* stream, size_t state_bytes, size_t aux_bytes, size_t 
     return VQE_OK;
 }
 
+// Whether the stream's scratch holds `bytes` or could grow to them.
+static int scratch_room(void* stream, size_t bytes, bool* room) {
+    int dev;
+    if (int rc = current_device(&dev)) return rc;
+    {
+        std::lock_guard<std::mutex> lk(g_ws_mu);
+        const auto it = g_ws.find({dev, stream});
+        *room = it != g_ws.end() && it->second && it->second->scratch_bytes >= bytes;
+    }
+    if (*room) return VQE_OK;
+    size_t fr = 0, tot = 0;
+    HIPCHK(hipMemGetInfo(&fr, &tot));
+    *room = bytes + (size_t(64) << 20) <= fr;
+    return VQE_OK;
+}
+
 // Bump allocator over a scratch block (256-byte aligned slices).
 struct Carver {
     char* base;
@@ -3599,7 +3615,9 @@ extern "C" int vqe_expectation(const vqe_state* s, const vqe_hamiltonian* H, dou
     // listed / all outputs, us: two-body Hamiltonians on 4 qubits 36 / 28, 12 qubits
     // 47 / 40, 14 qubits 50 / 46, 15 qubits 51 / 71, 16 qubits 52 / 129; 200 diagonal
     // strings on 15 qubits 43 / 44, 16 qubits 43 / 60
-    const bool listed = s->n <= 24 && double(N) * (double(H->c.size()) + 2000.0) > 1e8;
+    bool listed = s->n <= 24 && double(N) * (double(H->c.size()) + 2000.0) > 1e8;
+    if (listed)   // (1 MiB: the call's other buffers)
+        if (int rc = scratch_room(s->st, 4 * (N + nz_counts(N)) + (size_t(1) << 20), &listed)) return rc;
     StateCall c;
     if (int rc = begin_state_call(s, 0, 0, gx * gy, &c, listed ? N + nz_counts(N) : 0)) return rc;
     c.sd.chunks = hw->chunks;
