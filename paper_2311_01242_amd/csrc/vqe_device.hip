@@ -41,8 +41,8 @@ int enable_large_lds(size_t bytes);   // k_gates.hip
 
 // Launch parameters of one (qubit count, batched or single) configuration.
 struct Tuning {
-    int64_t fwd_budget;   // LDS bytes of a forward run tile
-    int64_t adj_budget;   // LDS bytes of a reverse run tile (phi + lambda)
+    int64_t fwd_budget;   // LDS bytes of a forward run tile; 0: by the program (tile_budget)
+    int64_t adj_budget;   // LDS bytes of a reverse run tile (phi + lambda); 0: by the program
     int L;                // low-bit tile of the sector H-apply
     int fwd_threads = 256; // packed layout: least threads per forward run tile
     int adj_threads = 256; // packed layout: least threads per reverse run tile
@@ -64,18 +64,7 @@ static Tuning default_tuning(int n, bool batched) {
         // a single state: 12 block bits (the packed layout raises L to n_e when
         // that is more)
         L = std::min(n, 12);
-        // full-vector runs: tiles small enough to give a lone state many
-        // workgroups, whole states up to 10 qubits.  Measured, forward tiles of
-        // 512 / 1024 / 2048 / 4096 amplitudes: 16-qubit UCCSD state and its
-        // energy 328 / 342 / 392 / 515 us, 18 qubits 759 / 513 / 571 / 711, 19
-        // qubits 1288 / 797 / 854 / 1019, 20 qubits 2594 / 1999 / 1404 / 1546;
-        // 400 Pauli rotations on 14 qubits with their gradient, forward and
-        // reverse tiles of 512 962 us, of 4096 and 2048 1585
-        if (n <= 20) {
-            const int amps = n <= 10 ? 1024 : n <= 17 ? 512 : n <= 19 ? 1024 : 2048;
-            t.fwd_budget = int64_t(amps) * 16;
-            t.adj_budget = int64_t(amps) * 32;
-        }
+        if (n <= 20) t.fwd_budget = t.adj_budget = 0;
     }
     t.L = L;
     // Runs whose H-apply does not depend on L (string products): L down to
@@ -423,9 +412,10 @@ static uint32_t pext_host(uint32_t v, uint32_t mask) {
 // the same created orbitals (key) whose tile of `vectors` statevectors fits
 // `budget` LDS bytes.  The tile's inner bits always include the lowest three
 // qubits (minus key bits) so that loads and stores move whole 128-byte lines.
+// tgs null: the split alone, without the gates' descriptors.
 static void plan_direction(const vqe_ansatz* A, int64_t budget, int vectors,
                            std::vector<std::pair<int, int>>& steps, std::vector<RunDesc>& runs,
-                           std::vector<int>& offs, std::vector<TileGate>& tgs, double& bytes) {
+                           std::vector<int>& offs, std::vector<TileGate>* tgs, double& bytes) {
     const int n = A->n;
     const uint32_t full = (n == 32) ? 0xffffffffu : ((1u << n) - 1u);
     const int64_t M = int64_t(A->gates.size());
@@ -472,8 +462,8 @@ static void plan_direction(const vqe_ansatz* A, int64_t budget, int vectors,
             r.contiguous = (inner == ((1u << r.m) - 1u)) ? 1 : 0;
             r.ntiles = int32_t(1u << __builtin_popcount(r.outer));
             r.kind = 1;
-            offs.push_back(int(tgs.size()));
-            for (int64_t k = j; k < j2; ++k) {
+            if (tgs) offs.push_back(int(tgs->size()));
+            for (int64_t k = j; tgs && k < j2; ++k) {
                 const GateDesc& h = A->gates[k];
                 TileGate t{};
                 t.xr = pext_host(h.x, inner);
@@ -481,7 +471,7 @@ static void plan_direction(const vqe_ansatz* A, int64_t budget, int vectors,
                 t.chr = uint32_t(__builtin_popcount(h.x & h.chain) & 3);
                 t.chain_out = h.chain & r.outer;
                 t.csign = 1.0;
-                tgs.push_back(t);
+                tgs->push_back(t);
             }
             steps.push_back({0, int(runs.size())});
             runs.push_back(r);
@@ -518,8 +508,8 @@ static void plan_direction(const vqe_ansatz* A, int64_t budget, int vectors,
         r.m = __builtin_popcount(inner);
         r.contiguous = (inner == ((1u << r.m) - 1u)) ? 1 : 0;
         r.ntiles = int32_t(1u << __builtin_popcount(r.outer));
-        offs.push_back(int(tgs.size()));
-        for (int64_t k = j; k < j2; ++k) {
+        if (tgs) offs.push_back(int(tgs->size()));
+        for (int64_t k = j; tgs && k < j2; ++k) {
             const GateDesc& h = A->gates[k];
             TileGate t{};
             t.xr = pext_host(h.pd, inner);
@@ -527,13 +517,64 @@ static void plan_direction(const vqe_ansatz* A, int64_t budget, int vectors,
             t.chr = pext_host(h.chain & inner, inner);
             t.chain_out = h.chain & r.outer;
             t.csign = h.csign;
-            tgs.push_back(t);
+            tgs->push_back(t);
         }
         steps.push_back({0, int(runs.size())});
         runs.push_back(r);
         bytes += 2.0 * double(tile_bytes(inner)) * double(r.ntiles);   // read + write every tile
         j = j2;
     }
+}
+
+// LDS budget of a lone state's full-vector tiles of `vectors` vectors, up to 20
+// qubits: of 512 amplitudes up to 64 KiB, the tile whose split takes the least
+// time by what the launches of one direction were measured to take, in us:
+//   a gate alone 2.9 sqrt(vectors) and its pass over memory at 2.2 TB/s;
+//   a run 2.5, its pass at 4 TB/s, 6 per 64 KiB of tile (one workgroup's loads
+//   and stores), 3 ns per tile; each gate 0.2 and 0.125 per 256 pairs of a tile,
+//   1.9 times that in reverse.
+// Small tiles give a lone state more workgroups and shorter steps, large ones
+// hold wider flip masks, so that fewer gates are alone and runs are longer; what
+// wins depends on the program's masks.  400 rotations, energy and gradient, us,
+// tiles of 512 / 1024 / 2048 / 4096 (reverse 2048 at most): 11 qubits, strings on
+// 1 to 4 qubits 719 / 737 / 817 / 818, on all 2771 / 2559 / 870 / 874; 12 qubits on
+// all 2963 / 3521 / 3801 / 2969 (forward alone 1304 / 1391 / 1381 / 541); 14 qubits
+// on 1 to 4 919 / 1012 / 1336 / 1533, on all 2946 / 3714 / 5484 / 6519.  States of
+// UCCSD, us: 16 qubits 262 / 279 / 326 / 449, 18 qubits 628 / 372 / 427 / 576, 20
+// qubits 1828 / 1237 / 618 / 758, Bravyi-Kitaev on 20 qubits (wider masks) 27.4 /
+// 18.7 / 13.6 / 11.7 ms.  Where the times are within 3%, the tile that is best for
+// narrow strings.  Over 130 such programs on 11 to 20 qubits the choice was within
+// 7% of the best tile and never more than 2% behind 64 KiB.
+static int64_t tile_budget(const vqe_ansatz* A, int vectors) {
+    const double N = double(uint64_t(1) << A->n);
+    if (A->n <= 10) return (int64_t(16) << 10) * vectors;   // the whole state
+    const int64_t narrow = A->n <= 17 ? 512 : A->n <= 19 ? 1024 : 2048;
+    int64_t best = 0;
+    double best_us = 0.0;
+    for (int64_t amps = 512; 16 * amps * vectors <= (64 << 10); amps *= 2) {
+        std::vector<std::pair<int, int>> steps;
+        std::vector<RunDesc> runs;
+        std::vector<int> offs;
+        double bytes = 0.0, us = 0.0;
+        plan_direction(A, 16 * amps * vectors, vectors, steps, runs, offs, nullptr, bytes);
+        for (const auto& st : steps)
+            if (st.first == 1) us += 2.9 * std::sqrt(double(vectors)) + 32.0 * N * vectors / 2.2e6;
+        for (const RunDesc& r : runs) {
+            const double tile = double(uint64_t(r.kind == 1 ? 1 : 2) << r.m);
+            us += 2.5 + 32.0 * N * vectors / 4e6 + 6.0 * 16.0 * tile * vectors / 65536.0 + 0.003 * r.ntiles;
+            for (int j = r.g0; j < r.g1; ++j) {
+                const double pairs = r.kind == 1 ? tile / 2 : double((uint64_t(1) << r.m) >> __builtin_popcount(A->gates[j].pd));
+                us += (0.2 + 0.125 * std::max(1.0, pairs / 256.0)) * (vectors == 2 ? 1.9 : 1.0);
+            }
+        }
+        if (amps == narrow) us *= 0.97;
+        if (best == 0 || us < best_us) {
+            best = 16 * amps * vectors;
+            best_us = us;
+        }
+        if (double(amps) >= N) break;
+    }
+    return best;
 }
 
 static int get_plan(const vqe_ansatz* A, DevAnsatz* da, const Tuning& tn, AnsatzPlan** out) {
@@ -545,11 +586,11 @@ static int get_plan(const vqe_ansatz* A, DevAnsatz* da, const Tuning& tn, Ansatz
         return VQE_OK;
     }
     auto* p = new AnsatzPlan();
-    p->fwd_budget = tn.fwd_budget;
-    p->adj_budget = tn.adj_budget;
+    p->fwd_budget = tn.fwd_budget > 0 ? tn.fwd_budget : tile_budget(A, 1);
+    p->adj_budget = tn.adj_budget > 0 ? tn.adj_budget : tile_budget(A, 2);
     std::vector<TileGate> tf, ta;
-    plan_direction(A, tn.fwd_budget, 1, p->fwd_steps, p->fwd_runs, p->fwd_off, tf, p->fwd_bytes);
-    plan_direction(A, tn.adj_budget, 2, p->adj_steps, p->adj_runs, p->adj_off, ta, p->adj_bytes);
+    plan_direction(A, p->fwd_budget, 1, p->fwd_steps, p->fwd_runs, p->fwd_off, &tf, p->fwd_bytes);
+    plan_direction(A, p->adj_budget, 2, p->adj_steps, p->adj_runs, p->adj_off, &ta, p->adj_bytes);
     const int n = A->n;
     const uint64_t N = uint64_t(1) << n;
     p->fwd_bytes += double(sizeof(double2)) * double(N);   // |HF> write

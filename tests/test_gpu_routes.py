@@ -2,12 +2,13 @@
 the profiler, by names."""
 import collections
 
+import numpy as np
 import pytest
 import torch
 from torch.profiler import ProfilerActivity, profile
 
 import paper_2311_01242_amd as vq
-from vqe_inputs import random_integrals
+from vqe_inputs import random_integrals, uniform_theta
 
 pytestmark = pytest.mark.gpu
 
@@ -35,3 +36,27 @@ def test_expectation_lists_nonzero_amplitudes(n, listed):
     s = vq.State.wrap(t)
     got = launches(lambda: s.expectation(H))
     assert got["k_hx_dense"] == 1 and got["k_nz_count"] == int(listed) and sum(got.values()) == (5 if listed else 2)
+
+
+def _rotations(n, gates, width, seed):
+    """Strings on `width` qubits (0: one to four), one angle each."""
+    rng = np.random.default_rng(seed)
+    x, z = np.zeros(gates, np.uint32), np.zeros(gates, np.uint32)
+    for i in range(gates):
+        for q in rng.choice(n, min(n, width or int(rng.choice([1, 2, 2, 2, 4]))), replace=False):
+            letter = int(rng.integers(1, 4))
+            x[i] |= np.uint32((letter & 1) << int(q))
+            z[i] |= np.uint32((letter >> 1) << int(q))
+    return vq.Ansatz.from_rotations(n, gates, x, z, np.arange(gates, dtype=np.int32), rng.uniform(0.5, 1.5, gates))
+
+
+@pytest.mark.parametrize("n,width,least,most", [(9, 9, 1, 4), (10, 10, 1, 8), (11, 6, 1, 8), (11, 9, 1, 8), (11, 11, 1, 8),
+                                                (14, 0, 16, 100), (16, 0, 16, 100)])
+def test_rotation_runs_follow_the_masks(n, width, least, most):
+    # wide strings: the tile is the whole state (400 gates in runs of up to 128); narrow ones: small tiles
+    H = vq.Hamiltonian.from_paulis(n, [0, 1], [1, 0], [1.0, 0.5])
+    A = _rotations(n, 400, width, n)
+    theta = uniform_theta(n, 400)
+    got = launches(lambda: vq.energy_grad(H, A, n // 2, theta))
+    assert least <= got["k_rot_fwd"] + got["k_pauli"] <= most
+    assert least <= got["k_rot_adj"] + got["k_adj_pauli"] <= most
