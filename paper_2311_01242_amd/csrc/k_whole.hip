@@ -15,7 +15,16 @@
 // 16 qubits, one state 369 -> 203 -> 192; 17 qubits, 60 states 615 -> 349 -> 357,
 // 400 states 1439 -> 677 -> 681; k-UpCCGSD (k = 2), 60 states, 16 qubits 304 ->
 // 222 -> 169, 17 qubits 425 -> 361 -> 346.  (14 qubits: the first figure is the
-// second form's.)  No size was found where the tiled runs win.
+// second form's.)
+// Against the tiled runs' present form (its best threads and block bits), whole
+// calls with gradient, us, here / tiled, 2 / 60 / 400 states: UCCSD 14 qubits 129 /
+// 176, 136 / 193, 187 / 332; 15 qubits 161 / 217, 179 / 260, 315 / 517; 16 qubits
+// 255 / 243, 289 / 329, 657 / 860; 17 qubits 418 / 282, 477 / 468, 1127 / 1456;
+// k-UpCCGSD 16 qubits 231 / 253, 262 / 297, 596 / 803; 17 qubits 402 / 293, 461 / 436,
+// 1104 / 1304; UCCSD on 20 qubits with 4 electrons (2,025 strings) 204 / 356, 216 /
+// 390, 307 / 801.  So a state alone on its compute unit is slower here in the
+// largest sectors only; lone states take tiles there (whole_as_tiles), batches
+// are not told apart by their number of states.
 #include "device_common.h"
 
 #include <algorithm>

@@ -75,7 +75,10 @@ static Tuning default_tuning(int n, bool batched) {
     // 55 x 19 L = 10 / 11 900 / 910, 49 x 20 L = 10 / 11 / 12 1575 / 1507 / 1736, 16 x 22
     // L = 11 / 12 2218 / 2513.  (24 qubits at half filling are at 12 anyway;
     // with 8 electrons 11 costs a pool's sweep 10%.)
+    // A lone 17-qubit state that takes tiles (whole_as_tiles), L = 8 / 9 / 10 / 11 / 12:
+    // UCCSD 310 / 301 / 306 / 338 / 379, k-UpCCGSD 336 / 329 / 293 / 309 / 310.
     if (n >= 18 && n <= 22) t.product_L = std::min(11, n / 2 + (batched ? 1 : 0));
+    if (n == 17 && !batched) t.product_L = 10;
     // Threads: a lone state's tiles leave most of the chip idle, so the steps'
     // latency counts, a batch's the waves' overhead.  256 -> 512 threads: one
     // state of 20 qubits 462 -> 431 us, 22 qubits 751 -> 695, but 24 qubits 1363
@@ -2990,6 +2993,22 @@ static bool sector_path(const vqe_ansatz* A, int ne) {
     return A->sector_conserving && A->n_electrons == ne;
 }
 
+// Whether a lone state whose sector fits one workgroup takes the tiled runs all
+// the same: its gates then have the chip instead of one compute unit.  That
+// pays where a gate's pairs fill the unit's LDS pipe for long, which they do in
+// the largest sectors.  Energy and gradient (energy alone), us, whole state / tiled
+// runs with 512 threads and their best block bits: 8,820 strings (17 qubits, 8
+// electrons) UCCSD 420 (170) / 278 (151), k-UpCCGSD (k = 2) 407 (154) / 286 (157), 40
+// single excitations 170 (77) / 114 (82), but 16 scattered operators 110 (59) / 131
+// (90); 9,075 strings (22 qubits, 5 electrons: 425 pairs a gate, more runs) 393
+// (160) / 556 (286); 7,056 strings (17 qubits, 7 electrons) UCCSD 337 (143) / 290 (158),
+// k-UpCCGSD 261 (115) / 281 (153), with 18 qubits and 6 electrons 332 (141) / 340
+// (182); 4,900 strings (16 qubits, 8 electrons) UCCSD 272 (116) / 240 (137), k-UpCCGSD 235
+// (104) / 244 (136); fewer strings: whole states by more.
+static bool whole_as_tiles(int64_t strings, int gates, double pairs) {
+    return strings > 8192 && pairs > 60000.0 && pairs > 600.0 * gates;
+}
+
 // force_L > 0: block bits of the packed layout (and sector H-apply tile)
 // regardless of the tuning (the persistent batch passes use one common value).
 // whole_ok: the caller can do without the block layout.
@@ -3029,14 +3048,8 @@ static int make_eval_plan(const vqe_ansatz* A, int ne, bool batched, EvalPlan* e
             if (product_L > 0) ep->hx.L = product_L;
             ep->hx.L = std::max(ep->hx.L, need);
         }
-        ep->hx.ntiles = 1 << (n - ep->hx.L);
-        ep->hx.na = (ne + 1) / 2;
-        ep->hx.nb = ne / 2;
-        if (int rc = hx_tables(ep->hx.L, &ep->hxt)) return rc;
-        ep->nblk_e = ep->hx.ntiles;
-        // a sector that fits one workgroup: whole-state passes (faster at every
-        // size measured, e.g. 16 qubits, one state: 192 us of both passes against
-        // 369 with tiled runs), unless a largest tile below it was asked for
+        // a sector that fits one workgroup: whole-state passes, unless a largest
+        // tile below it was asked for or whole_as_tiles says otherwise
         if (ep->packed && whole_ok && g_packed_enabled.load() >= 2 && g_real_enabled.load() != 0 &&
             (n + 1) / 2 <= kCiMaxBits) {
             const int64_t size = binom((n + 1) / 2, (ne + 1) / 2) * binom(n / 2, ne / 2);
@@ -3049,6 +3062,10 @@ static int make_eval_plan(const vqe_ansatz* A, int ne, bool batched, EvalPlan* e
                 args.nsplit = batched ? 1 : ci_choose_splits(args);
                 if (int rc = whole_plan(A, da, *cs, uint32_t((uint64_t(1) << ne) - 1), kWholeFit, &ep->whole)) return rc;
                 if (ep->whole->args.threads == 0 || ci_prepare(args) != 0) ep->whole = nullptr;
+            }
+            if (ep->whole && !batched && whole_as_tiles(size, ep->M, ep->whole->pairs)) {
+                ep->whole = nullptr;
+                ep->hx.L = std::max(tn.product_L > 0 ? tn.product_L : ep->hx.L, need);
             }
             if (ep->whole) {
                 ep->ci = ep->real = true;
@@ -3065,6 +3082,11 @@ static int make_eval_plan(const vqe_ansatz* A, int ne, bool batched, EvalPlan* e
                 return VQE_OK;
             }
         }
+        ep->hx.ntiles = 1 << (n - ep->hx.L);
+        ep->hx.na = (ne + 1) / 2;
+        ep->hx.nb = ne / 2;
+        if (int rc = hx_tables(ep->hx.L, &ep->hxt)) return rc;
+        ep->nblk_e = ep->hx.ntiles;
         if (ep->packed) {
             if (int rc = packed_layout(n, ne, ep->hx.L, &ep->lay)) return rc;
             if (int rc = packed_plan(A, da, *ep->lay, tn, force_L == 0, &ep->pp)) return rc;

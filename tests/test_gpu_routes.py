@@ -60,3 +60,22 @@ def test_rotation_runs_follow_the_masks(n, width, least, most):
     got = launches(lambda: vq.energy_grad(H, A, n // 2, theta))
     assert least <= got["k_rot_fwd"] + got["k_pauli"] <= most
     assert least <= got["k_rot_adj"] + got["k_adj_pauli"] <= most
+
+
+@pytest.mark.parametrize("n,ne,kind,tiled", [(16, 8, "uccsd", False), (17, 8, "uccsd", True), (17, 8, "kup", True),
+                                             (17, 9, "kup", True), (17, 7, "kup", False), (17, 8, "few", False),
+                                             (22, 5, "uccsd", False)])
+def test_lone_states_in_large_sectors_take_tiles(n, ne, kind, tiled):
+    H = vq.Hamiltonian.from_integrals(n, *random_integrals(n, 4800 + n))
+    A = vq.Ansatz.kupccgsd(n, ne, 2) if kind == "kup" else vq.Ansatz.uccsd(n, ne)
+    if kind == "few":
+        A = A.select(np.arange(0, A.n_params, 30, dtype=np.int32))
+    theta = uniform_theta(n, A.n_params)
+    value = []
+    got = launches(lambda: value.append(vq.energy_grad(H, A, ne, theta)))
+    assert (got["k_prun"] > 0) == tiled and got["k_whole_fwd"] == got["k_whole_adj"] == int(not tiled)
+    # a batch member of the same kind: whole states; sums in another order (2^-52 * 100 * sqrt(9075) = 2e-12)
+    b = vq.Batch([H] * 2, [A] * 2, [ne] * 2)
+    eb, gb = b.energy_grad(np.tile(theta, 2))
+    b.close()
+    assert np.abs(eb - value[0][0]).max() < 1e-11 and np.abs(gb.reshape(2, -1) - value[0][1]).max() < 1e-11
