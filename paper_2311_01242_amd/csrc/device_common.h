@@ -771,7 +771,7 @@ int blocks_for(uint64_t work);
 // low half), swapped where the pair's sign is negative; places without a pair
 // have two of the kWholeIdle dummies after the amplitudes.
 constexpr int kWholeMax = 10000;   // amplitudes: phi and lambda side by side in 160 KiB
-constexpr int kWholeIdle = 128;
+constexpr int kWholeIdle = 2;
 constexpr int kWholePlaces = 4;    // most places per thread of a gate step without waits
 constexpr int kWholeWaves = 16;    // most waves of a pass (the gradient's partials per gate)
 
