@@ -379,6 +379,10 @@ int mm_prepare(CiMmArgs* mm) {
 }
 
 void launch_hx_mm(const StateDesc* sd, int count, const CiMmArgs& mm, hipStream_t st) {
+    const MmShape* sh = mm_shape(mm);
+    // (24 qubits: 4,536 states of 924 rows with 1,024 threads each)
+    for (const int most = states_per_launch(int64_t(mm.na_str) * 64 * sh->w); count > most; count -= most, sd += most)
+        launch_hx_mm(sd, most, mm, st);
     // 64 x 64 tiles when those fill the chip, else 16 x 16 with the inner
     // dimension split over the waves
     const int t64 = ((mm.na_str + 63) / 64) * ((mm.nb_str + 63) / 64);
@@ -393,7 +397,6 @@ void launch_hx_mm(const StateDesc* sd, int count, const CiMmArgs& mm, hipStream_
         hipLaunchKernelGGL(k_hx_same<2>, grid(ntm * ntn), dim3(256), 0, st, sd, mm, xs, ntn, ntm * ntn);
     else
         hipLaunchKernelGGL(k_hx_same_split<4>, grid(ntm * ntn), dim3(256), 0, st, sd, mm, xs, ntn, ntm * ntn);
-    const MmShape* sh = mm_shape(mm);
     const size_t lds = mm_lds(mm, *sh);
 #define VQE_MM_LAUNCH(W, NT, KS)                                                                              \
     if (sh->w == W && sh->nt == NT && sh->ks == KS)                                                           \

@@ -1,11 +1,12 @@
-// LDS of a tiled run (k_prun), in bytes from its start.  Host code only needs
-// the total; no HIP types, so that a plain C++ compiler can check it.
+// Sizes of launches as plain C++, so that a host compiler can check them.
 #pragma once
 
 #include <cstddef>
+#include <cstdint>
 
 namespace vqe {
 
+// LDS of a tiled run (k_prun), in bytes from its start.
 struct RunLds {
     size_t par;     // (cos, sgn sin) and (sgn, 0) of gate j at par + 32 j
     size_t wsum;    // reverse sweep: wave totals [gates][waves]
@@ -22,6 +23,13 @@ constexpr RunLds tiled_run_lds(int vectors, size_t vbytes, int entries, int gate
     l.wsum = l.par + 32 * size_t(gates) + 16;
     l.total = l.wsum + (vectors == 2 ? 8 * size_t(gates) * size_t(waves) : 0);
     return l;
+}
+
+// States that one launch may hold when each takes `threads` threads of the grid's
+// x dimension: HIP takes less than 2^32 of them; a multiple of 8 (states by XCD).
+constexpr int states_per_launch(int64_t threads) {
+    const int64_t most = int64_t(0xffffffffu) / (threads < 1 ? 1 : threads) / 8 * 8;
+    return int(most < 8 ? 8 : most > (1 << 30) ? (1 << 30) : most);
 }
 
 }  // namespace vqe
