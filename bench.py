@@ -180,21 +180,25 @@ def amp_dtype(real):
     return "float64" if real else "complex128"
 
 
-# phase -> (kernel, source file, bound)
+# phase -> (kernel, source files, bound)
 PHASE_KERNELS = {
     "forward": ("k_prun<1,*,*> (packed forward gate runs; k_whole_fwd for sectors of one workgroup)",
-                "k_packed.hip", "hbm"),
+                ("k_packed.hip", "k_whole.hip"), "hbm"),
     "h_apply": ("k_hx_same + k_hx_cross (string-product sector H-apply as FP64 matrix products; k_hx_ci for small "
-                "sectors and Hamiltonians without that form; with the order conversions)", "k_hx_mm.hip", "alu"),
+                "sectors and Hamiltonians without that form; with the order conversions)", ("k_hx_mm.hip", "k_hx_ci.hip"), "alu"),
     "adjoint": ("k_prun<2,*,*> (packed reverse-sweep gate runs; k_whole_adj for sectors of one workgroup)",
-                "k_packed.hip", "hbm"),
+                ("k_packed.hip", "k_whole.hip"), "hbm"),
 }
 
 
-def source_hash(name):
+def source_hash(names):
+    """sha256 of a kernel source, or of several one after the other."""
     import hashlib
-    with open(os.path.join(CSRC, name), "rb") as f:
-        return hashlib.sha256(f.read()).hexdigest()
+    h = hashlib.sha256()
+    for name in [names] if isinstance(names, str) else names:
+        with open(os.path.join(CSRC, name), "rb") as f:
+            h.update(f.read())
+    return h.hexdigest()
 
 
 def _binom(n, k):
@@ -281,8 +285,7 @@ def cpu_model():
 def add_ceiling_fracs(roof, ceilings):
     """Fractions of the HBM-bound phases' achieved GB/s against the measured
     copy ceilings (the vendor-peak fraction stays in `frac`), and of the
-    packed gate runs' LDS traffic and the string-product H-apply's beta-pair
-    gathers against the measured LDS ceiling."""
+    packed gate runs' LDS traffic against the measured LDS ceiling."""
     for rec in [roof] + list(roof.get("phases", {}).values()):
         if rec.get("bound") == "hbm" and rec.get("unit") == "GB/s":
             rec["frac_copy_64MB"] = round(rec["achieved"] / ceilings["copy_64MB"]["GB/s"], 4)
@@ -724,7 +727,7 @@ def run_mlp16(args):
         "higher_is_better": True, "scaling": "weak", "vs_baseline": None, "dtype": "bf16 (products) / fp32",
         "data": "synthetic",
         "config": {"workload": "warm-start MLP 37-256-256-360 trained on 160 samples (16-qubit shapes)"},
-        "roofline": {"bound": "mfma", "kernel": "k_mlp_fwd + k_mlp_back (v_mfma_f32_16x16x32_bf16)",
+        "roofline": {"bound": "mfma", "kernel": "k_mlp_fwd + k_mlp_back + k_mlp_update (v_mfma_f32_16x16x32_bf16)",
                      "achieved": round(achieved, 3), "peak": BF16_PEAK_TFLOPS, "unit": "TFLOP/s",
                      "frac": round(achieved / BF16_PEAK_TFLOPS, 6), "traffic": None,
                      "algorithmic_flops_per_step": flops},

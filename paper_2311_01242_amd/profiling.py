@@ -14,7 +14,7 @@ Three sub-commands, both reading the CSV files rocprofv3 writes with
             what the same counters read for a plain device copy of known size
             (``bench.py --calibrate-copy``: 3 copies of 2 GiB).  Writes the
             JSON that ``bench.py`` reads for ``roofline.traffic`` (keyed by
-            phase, with the sha256 of the kernel source it was measured on)
+            phase, with the sha256 of the kernel sources it was measured on)
             and prints a markdown table.
 
 Phase of a kernel: k_prun<1,...> / k_whole_fwd / k_run_fwd / k_small_fwd
@@ -34,7 +34,9 @@ import os
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_2311_01242_amd", "csrc")
-PHASE_SOURCE = {"forward": "k_packed.hip", "adjoint": "k_packed.hip", "h_apply": "k_hx_mm.hip"}
+# the sources of a phase's kernels on the packed layout (batch512, single24)
+PHASE_SOURCE = {"forward": ("k_packed.hip", "k_whole.hip"), "adjoint": ("k_packed.hip", "k_whole.hip"),
+                "h_apply": ("k_hx_mm.hip", "k_hx_ci.hip")}
 COPY_BYTES = 2 ** 31
 
 
@@ -94,9 +96,12 @@ def _sum_counter(path):
     return tot, cnt
 
 
-def _sha(name):
-    with open(os.path.join(CSRC, name), "rb") as f:
-        return hashlib.sha256(f.read()).hexdigest()
+def _sha(names):
+    h = hashlib.sha256()
+    for name in names:
+        with open(os.path.join(CSRC, name), "rb") as f:
+            h.update(f.read())
+    return h.hexdigest()
 
 
 def cmd_traffic(args):
@@ -121,7 +126,7 @@ def cmd_traffic(args):
         write = w.get(ph, 0.0) * 1024 * kw / args.evals
         launches = fc[ph] / args.evals
         per = (fetch + write) / launches
-        out["kernels"][ph] = {"source_sha256": _sha(PHASE_SOURCE[ph]), "source": PHASE_SOURCE[ph],
+        out["kernels"][ph] = {"source_sha256": _sha(PHASE_SOURCE[ph]), "source": list(PHASE_SOURCE[ph]),
                               "fetch_bytes_per_eval": fetch, "write_bytes_per_eval": write,
                               "launches_per_eval": launches, "bytes_per_launch": per}
         print(f"| {ph} | {launches:.0f} | {fetch / 1e9:.2f} | {write / 1e9:.2f} | {per / 1e6:.2f} MB |")
