@@ -345,8 +345,9 @@ int vqe_batch_profile(vqe_batch* b, const double* theta_all, int reps, double* m
  * plan (8 doubles): w[0] forward-sweep bytes (each run tile read and written
  * once, plus the |HF> write), w[1] pair updates of one pass over the gates
  * on the packed layout (live tiles; the reverse sweep makes as many), w[2]
- * reverse-sweep bytes (phi and
- * lambda tiles read and written once), w[3] bytes of all phi + lambda,
+ * reverse-sweep bytes (phi and lambda tiles read and written once; states held
+ * whole by one workgroup write phi forward and read phi and lambda in reverse),
+ * w[3] bytes of all phi + lambda,
  * w[4] gate-step launches of the forward sweep, w[5] H-apply launches,
  * w[6] gate-step launches of the reverse sweep, w[7] states evaluated with
  * real amplitudes (vqe_set_real). */
@@ -355,7 +356,11 @@ int vqe_batch_work(const vqe_batch* b, double* w);
 /* Launch-parameter override for states of n_qubits (batched = 1 for batch
  * members, 0 for single-state calls): LDS bytes of a forward and a reverse
  * run tile (4 KiB .. 160 KiB) and the low-bit tile of the sector H-apply
- * (2 .. 14).  All three <= 0 restores the built-in choice.  Applies to plans
+ * (2 .. 14).  All three <= 0 restores the built-in choice (single states of up
+ * to 20 qubits: run tiles of 512 amplitudes up to 64 KiB, by the program's flip
+ * masks).  On the packed sector layout the run budgets play no part and
+ * hx_tile_bits is the number of block bits; without effect on evaluations that
+ * hold a whole state in one workgroup (vqe_set_tile_cap).  Applies to plans
  * made after the call (batches created later, later single-state calls). */
 int vqe_set_tuning(int n_qubits, int batched, int64_t fwd_lds_bytes, int64_t adj_lds_bytes,
                    int hx_tile_bits);
@@ -365,8 +370,9 @@ int vqe_set_tuning(int n_qubits, int batched, int64_t fwd_lds_bytes, int64_t adj
  * run tile (64, 256, 512 or 1024) of the forward and of the reverse pass;
  * a tile too large for that count with the available shapes uses fewer
  * threads with more entries each.  Both <= 0 restores the built-in choice
- * (64 for batch members, 256 for single states).  Applies to plans made after
- * the call.  Errors: ERANGE. */
+ * (256; 512 for single states of 16 to 22 qubits).  Without effect on
+ * evaluations that hold a whole state in one workgroup (vqe_set_tile_cap).
+ * Applies to plans made after the call.  Errors: ERANGE. */
 int vqe_set_run_threads(int n_qubits, int batched, int fwd_threads, int adj_threads);
 
 /* Evaluation layout switch (process-wide, default 2).  With 1 or 2, energy
@@ -400,7 +406,16 @@ int vqe_set_real(int on);
  * outside the window; entries (16..8192) bounds the largest tile, so that
  * fewer block bits with more window bits mean fewer runs (fewer passes over
  * the state) at the same tile size.  0 restores the default: 2400 entries,
- * or two of the layout's largest blocks when they hold more.  Errors: ERANGE. */
+ * or two of the layout's largest blocks when they hold more.
+ * A cap below the number of a sector's amplitudes also selects the tiled runs
+ * where a whole state would otherwise be held by one workgroup: energies and
+ * gradients of real amplitudes in mode 2 of vqe_set_packed whose sector has at
+ * most 10,000 amplitudes (17 qubits at half filling) and leaves room for the
+ * program's angles (16 bytes a gate) in 160 KiB, except single states in the
+ * largest of these sectors and pool gradients, which take tiles anyway.  (A cap
+ * tuned before whole-state evaluations existed, typically 1600 to 3200, keeps
+ * sizes up to 17 qubits on the tiled runs until it is reset to 0.)
+ * Errors: ERANGE. */
 int vqe_set_tile_cap(int n_qubits, int batched, int entries);
 
 /* Persistent batch passes (process-wide, applies to batches created after

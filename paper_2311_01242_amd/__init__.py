@@ -29,13 +29,17 @@ __all__ = [
 
 def set_tuning(n_qubits: int, batched: bool, fwd_lds_bytes: int = 0, adj_lds_bytes: int = 0,
                hx_tile_bits: int = 0):
-    """Override the launch parameters for n_qubits (all zeros: built-in choice)."""
+    """Override the launch parameters for n_qubits (all zeros: built-in choice).
+    Without effect on evaluations that hold a whole state in one workgroup
+    (see set_tile_cap)."""
     _check(lib().vqe_set_tuning(int(n_qubits), int(bool(batched)), int(fwd_lds_bytes),
                                 int(adj_lds_bytes), int(hx_tile_bits)))
 
 
 def set_run_threads(n_qubits: int, batched: bool, fwd_threads: int = 0, adj_threads: int = 0):
-    """Least threads per packed run tile (64/256/512/1024; zeros: built-in)."""
+    """Least threads per packed run tile (64/256/512/1024; zeros: built-in, 256 or,
+    for single states of 16 to 22 qubits, 512).  Without effect on evaluations
+    that hold a whole state in one workgroup (see set_tile_cap)."""
     _check(lib().vqe_set_run_threads(int(n_qubits), int(bool(batched)), int(fwd_threads),
                                      int(adj_threads)))
 
@@ -69,7 +73,11 @@ def real_enabled():
 def set_tile_cap(n_qubits: int, batched: bool, entries: int = 0):
     """Largest packed run tile (entries per vector) for n_qubits; 0 = the
     default (2400 entries, or two of the layout's largest blocks when they
-    hold more).  Applies to plans made afterwards."""
+    hold more).  A cap below a sector's number of amplitudes also selects the
+    tiled runs where one workgroup would otherwise hold the whole state (real
+    amplitudes, at most 10,000 of them: up to 17 qubits at half filling); caps
+    tuned for such sizes earlier keep them on tiles until set to 0.  Applies to
+    plans made afterwards."""
     _check(lib().vqe_set_tile_cap(int(n_qubits), int(bool(batched)), int(entries)))
 
 
