@@ -48,13 +48,13 @@ __global__ void k_packed_hf(const StateDesc* __restrict__ sd, int64_t size) {
 // loads before the first gate, then each wave's serial instruction stream.  A
 // gate took 436 cycles, 328 of them without its pair's work: address and clamp
 // arithmetic, two branches, a parity test; barriers and bank conflicts next to
-// nothing.  Hence a step of 20 instructions without a branch (an entry is two
-// LDS offsets, the sign their order, absent pairs a dummy), and, as the waits
-// that remain are then the barriers', waves that own whole groups of strings
-// (WaveSplit in vqe_device.hip) and meet once per stretch of gates.  Forward +
-// reverse, us: one state of 18 qubits 281 -> 243, 20 qubits 432 -> 356, 22 qubits 690 ->
-// 577, 24 qubits 1363 -> 1277; 49 states of 20 qubits, where LDS is busy half
-// of the time, 1507 -> 1481.
+// nothing.  Hence a step of 20 instructions that branches only to a barrier (an
+// entry is two LDS offsets, the sign their order, absent pairs a dummy), and, as
+// the waits that remain are then the barriers', waves that own whole groups of
+// strings (WaveSplit in vqe_device.hip) and meet once per stretch of gates.
+// Forward + reverse, us: one state of 18 qubits 281 -> 243, 20 qubits 432 -> 356,
+// 22 qubits 690 -> 577, 24 qubits 1363 -> 1277; 49 states of 20 qubits, where LDS is
+// busy half of the time, 1507 -> 1481.
 template <int VEC, int BS, int EPT, typename V>
 __global__ void __launch_bounds__(BS) k_prun(const StateDesc* __restrict__ sd, PackedRun run,
                                              const PackedGate* __restrict__ pg) {
@@ -183,9 +183,9 @@ __global__ void __launch_bounds__(BS) k_prun(const StateDesc* __restrict__ sd, P
     // one gate: its pairs (one per thread per pass), returning the thread's
     // part of the gate's total; the slot's entry for gate t + kListAhead is
     // loaded meanwhile, and the next gate's (cos, sgn sin) read.  A place
-    // without a pair rotates the idle pair, so the step has no branch: what
-    // bounds it is the wave's serial instruction stream (about 16 per gate at 10 to
-    // 20 cycles each), not its LDS accesses or arithmetic.  LONG (a list
+    // without a pair rotates the idle pair, so the step branches only to a
+    // barrier: what bounds it is the wave's serial instruction stream (about 20 per
+    // gate forward, 10 to 20 cycles each), not its LDS accesses or arithmetic.  LONG (a list
     // longer than its span): the thread's later entries are read in the gate
     // itself; the gate loops are built separately for the two cases, so that
     // the common one has no other list reads than the slots'.  Between gates
