@@ -1619,8 +1619,11 @@ static int ci_matrix(const vqe_hamiltonian* H, CiHam* c, const CiSpace& cs, cons
     if (!cs.mm_ok || !c->diag.on || !c->psplit || !c->rgroups_h.empty() || !c->groups_h.empty()) return VQE_OK;
     const int oa = cs.oa, ob = cs.ob, pa = oa * (oa - 1) / 2, n = H->n;
     const int Mp = cs.mm.m_pad, NAp = cs.mm.na_pad, NBp = cs.mm.nb_pad;
-    double big = 0.0;
-    for (double v : H->tabs) big = std::max(big, std::fabs(v));
+    double big = 0.0;   // of the flips (not the diagonal: a constant has no part in them)
+    for (const GroupDesc& g : H->groups)
+        for (int si = g.sub_begin; g.x != 0 && si < g.sub_end; ++si)
+            for (int t = 0; t < (1 << (g.pos & 7)); ++t)
+                big = std::max(big, std::fabs(H->tabs[size_t(H->subs[size_t(si)].tab + t)]));
     const double tol = 1e-14 * big;
     auto par = [](uint32_t v) { return (__builtin_popcount(v) & 1) != 0; };
     // beta orbitals whose occupation crosses an alpha flip mask x, and the reverse

@@ -79,3 +79,56 @@ def test_lone_states_in_large_sectors_take_tiles(n, ne, kind, tiled):
     eb, gb = b.energy_grad(np.tile(theta, 2))
     b.close()
     assert np.abs(eb - value[0][0]).max() < 1e-11 and np.abs(gb.reshape(2, -1) - value[0][1]).max() < 1e-11
+
+
+def _near_two_body(n, kind):
+    """A Hamiltonian near one of two-body integrals: that one (plain), or one without a matrix form."""
+    x, z, c = vq.Hamiltonian.from_integrals(n, *random_integrals(n, 77)).terms()
+    keep = np.ones(x.size, bool)
+    pairs = [k for k in range(x.size) if bin(int(x[k]) & 0xAAAAAAAA).count("1") == 2 and
+             bin(int(x[k]) & 0x55555555).count("1") == 2]
+    xa, xb = int(x[pairs[0]]) & 0x55555555, int(x[pairs[0]]) & 0xAAAAAAAA
+    if kind in ("direction", "constant"):   # a double excitation whose coefficient depends on the hops' directions,
+        x = np.append(x, x[pairs[0]])       # with "constant" by little beside a constant that dwarfs all others
+        z = np.append(z, z[pairs[0]] ^ np.uint32(xa & -xa) ^ np.uint32(xb & -xb))
+        c = np.append(c, 0.3 if kind == "direction" else 1e-5)
+        keep = np.ones(x.size, bool)
+        if kind == "constant":
+            c[(x == 0) & (z == 0)] += 1e10
+    elif kind == "chain":        # a sign mask that is no Jordan-Wigner chain
+        free = ~(int(x[pairs[0]])) & ((1 << n) - 1)
+        z[x == x[pairs[0]]] ^= np.uint32(free & -free)
+    elif kind == "diagonal":     # a three-orbital Z string
+        x, z, c = np.append(x, np.uint32(0)), np.append(z, np.uint32(0b10110)), np.append(c, 0.37)
+        keep = np.ones(x.size, bool)
+    return vq.Hamiltonian.from_paulis(n, x[keep], z[keep], c[keep])
+
+
+@pytest.mark.parametrize("kind", ["plain", "direction", "constant", "chain", "diagonal"])
+@pytest.mark.parametrize("n,ne", [(12, 6), (15, 6), (18, 9)])
+def test_hamiltonians_without_matrix_form_are_walked(n, ne, kind):
+    # 2^-52 * 100 * sqrt(2000) = 1e-12 as for any two forms of the H-apply, 1e-11 allowed; with the
+    # constant a gradient component sums products of amplitudes with rounding errors of 2^-53 1e10 = 1e-6
+    tol = 1e-5 if kind == "constant" else 1e-11
+    H = _near_two_body(n, kind)
+    A = vq.Ansatz.uccsd(n, ne)
+    theta = uniform_theta(5, A.n_params, -0.3, 0.3)
+    value = []
+    got = launches(lambda: value.append(vq.energy_grad(H, A, ne, theta)))
+    assert (got["k_hx_cross"] > 0) == (kind == "plain") and (got["k_hx_ci"] > 0) == (kind != "plain")
+    vq.set_packed(False)
+    try:
+        e, g = vq.energy_grad(H, A, ne, theta)
+    finally:
+        vq.set_packed(True)
+    assert abs(value[0][0] - e) < max(tol, 1e-15 * abs(e) * 100) and np.abs(value[0][1] - g).max() < tol
+
+
+@pytest.mark.parametrize("n", [12, 13, 14, 16, 17, 19, 20, 22, 23, 24])
+def test_two_body_hamiltonians_have_the_matrix_form(n):
+    A = vq.Ansatz.uccsd(n, n // 2).select(np.arange(2, dtype=np.int32))
+    for seed in range(3):
+        h0, h, g = random_integrals(n, 5300 + seed)
+        H = vq.Hamiltonian.from_integrals(n, h0 + 1e3, 10.0 ** (seed - 1) * h, g)
+        got = launches(lambda: vq.energy_grad(H, A, n // 2, np.array([0.1, -0.2])))
+        assert got["k_hx_cross"] > 0 and got["k_hx_ci"] == 0
