@@ -19,15 +19,21 @@
 
 namespace vqe {
 
-// A workgroup takes sets of 64 R outputs (list[o], or o without a list), its
-// four waves every fourth group of the Hamiltonian's chunks hc = blockIdx.y,
-// blockIdx.y + gridDim.y, ..., which are staged in LDS; LAM: the waves' parts
-// of lambda are added in wave order and written (gridDim.y is 1).  A lane's
-// partner amplitudes of the next group are read during the current one.  The
-// groups' descriptors and tables read from memory one after the other, each
-// group was three dependent round trips to L2: lambda of a 14-qubit state (2.2k
-// strings) 350 -> 82 us, the energy of an 18-qubit UCCSD state (15,876 of
-// 262,144 amplitudes nonzero, 8.9k strings) 1431 -> 87 us with its list.
+// A workgroup takes the outputs o (list[o] with a list) and the Hamiltonian's
+// chunks hc = blockIdx.y, blockIdx.y + gridDim.y, ..., which are staged in LDS.
+// Each of its waves takes 64 R outputs, or, where fewer than kDenseSets
+// workgroups would have any, the four share them and take every fourth group;
+// LAM: their parts of lambda are then added in wave order (gridDim.y is 1).
+// Fewer groups than waves are not shared out.  (With the groups always shared by
+// four waves and a grid of 256 workgroups, the energy of one diagonal string on 24
+// qubits took 739 us, of 200 6378, of 20 strings that flip 1290; one output per
+// thread 80, 2817 and 788; so 83, 785 and 832.)  A lane's partner amplitudes of
+// the next group are read during the current one.  The groups' descriptors and
+// tables read from memory one after the other, each group was three dependent
+// round trips to L2: lambda of a 14-qubit state (2.2k strings) 350 -> 82 us, the
+// energy of an 18-qubit UCCSD state (15,876 of 262,144 amplitudes nonzero, 8.9k
+// strings) 1431 -> 87 us with its list.
+constexpr int kDenseSets = 1024;   // four workgroups per compute unit
 template <int R, bool LAM>
 __global__ void __launch_bounds__(kBlock) k_hx_dense(const StateDesc* __restrict__ sd, uint64_t N,
                                                      const uint32_t* __restrict__ list,
@@ -42,8 +48,13 @@ __global__ void __launch_bounds__(kBlock) k_hx_dense(const StateDesc* __restrict
     const double2* __restrict__ phi = s.phi;
     const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const uint64_t K = list ? uint64_t(*list_count) : N;
+    const bool split = s.G >= kW && K <= uint64_t(kDenseSets - 1) * kBlock * R;
+    const uint64_t set = split ? 64 * R : kBlock * R;   // outputs of the workgroup at a time
+    const int g0 = split ? w : 0, gstep = split ? kW : 1;
+    int staged = -1, ng = 0;   // the chunk in LDS, its groups
     double acc = 0.0;
-    for (uint64_t o0 = uint64_t(blockIdx.x) * 64 * R; o0 < K; o0 += uint64_t(gridDim.x) * 64 * R) {
+    for (uint64_t s0 = blockIdx.x * set; s0 < K; s0 += gridDim.x * set) {
+        const uint64_t o0 = split ? s0 : s0 + 64 * R * w;   // of the wave (K or more: none)
         uint32_t b[R];
         double lr[R], li[R];
 #pragma unroll
@@ -53,27 +64,33 @@ __global__ void __launch_bounds__(kBlock) k_hx_dense(const StateDesc* __restrict
             lr[r] = li[r] = 0.0;
         }
         for (int hc = blockIdx.y; hc < s.nb; hc += gridDim.y) {
-            const HxChunk ck = ldc(s.chunks + hc);
-            const int ng = ck.cg1 - ck.cg0, ns = ck.cs1 - ck.cs0, nt = ck.t1 - ck.t0;
-            __syncthreads();
-            for (int i = tid; i < ng; i += kBlock) gch[i] = s.cgroups[ck.cg0 + i];
-            for (int i = tid; i < ns; i += kBlock) sch[i] = s.csubs[ck.cs0 + i];
-            for (int i = tid; i < nt; i += kBlock) tch[i] = s.tabs[ck.t0 + i];
-            __syncthreads();
+            if (hc != staged) {
+                const HxChunk ck = ldc(s.chunks + hc);
+                const int ns = ck.cs1 - ck.cs0, nt = ck.t1 - ck.t0;
+                ng = ck.cg1 - ck.cg0;
+                __syncthreads();
+                for (int i = tid; i < ng; i += kBlock) gch[i] = s.cgroups[ck.cg0 + i];
+                for (int i = tid; i < ns; i += kBlock) sch[i] = s.csubs[ck.cs0 + i];
+                for (int i = tid; i < nt; i += kBlock) tch[i] = s.tabs[ck.t0 + i];
+                __syncthreads();
+                staged = hc;
+            }
             auto uniform = [](uint32_t v) { return uint32_t(__builtin_amdgcn_readfirstlane(int(v))); };
             double2 next[R];
-            if (w < ng) {
-                const uint32_t x = uniform(gch[w].x);
+            if (g0 < ng) {
+                const uint32_t x = uniform(gch[g0].x);
 #pragma unroll
                 for (int r = 0; r < R; ++r) next[r] = ldg2(phi + (b[r] ^ x));
             }
-            for (int gi = w; gi < ng; gi += kW) {
+            for (int gi = g0; gi < ng; gi += gstep) {
                 double2 p[R];
 #pragma unroll
                 for (int r = 0; r < R; ++r) p[r] = next[r];
-                const uint32_t xn = uniform(gch[min(gi + kW, ng - 1)].x);
+                if (gi + gstep < ng) {
+                    const uint32_t xn = uniform(gch[gi + gstep].x);
 #pragma unroll
-                for (int r = 0; r < R; ++r) next[r] = ldg2(phi + (b[r] ^ xn));
+                    for (int r = 0; r < R; ++r) next[r] = ldg2(phi + (b[r] ^ xn));
+                }
                 const uint32_t pos = uniform(gch[gi].pos);
                 const int s0 = int(uniform(uint32_t(gch[gi].sub_begin))), s1 = int(uniform(uint32_t(gch[gi].sub_end)));
                 const int k = int(pos & 7u);
@@ -105,7 +122,7 @@ __global__ void __launch_bounds__(kBlock) k_hx_dense(const StateDesc* __restrict
                 }
             }
         }
-        if constexpr (LAM) {
+        if (LAM && split) {
 #pragma unroll
             for (int r = 0; r < R; ++r) part[w][64 * r + lane] = make_double2(lr[r], li[r]);
             __syncthreads();
@@ -120,10 +137,12 @@ __global__ void __launch_bounds__(kBlock) k_hx_dense(const StateDesc* __restrict
                     acc += q.x * l.x + q.y * l.y;
                 }
             }
+            __syncthreads();   // part is read
         } else {
 #pragma unroll
             for (int r = 0; r < R; ++r)
                 if (o0 + 64 * r + lane < K) {
+                    if (LAM) s.lam[o0 + 64 * r + lane] = make_double2(lr[r], li[r]);
                     const double2 q = ldg2(phi + b[r]);
                     acc += q.x * lr[r] + q.y * li[r];
                 }
@@ -537,11 +556,13 @@ void launch_hx_dense(const StateDesc* sd, int count, uint64_t N, int nblk, int w
 }
 
 // Grid of the expectation value: the outputs' blocks, and the Hamiltonian's
-// chunks (few outputs, as in a sector's state, leave the chip idle alone).
+// chunks (few outputs, as in a sector's state, leave the chip idle alone).  Few
+// chunks: 2,048 workgroups, as many waves as the chip holds (4,096 cost 5 us more in
+// the partials' sum).
 void expect_grid(uint64_t N, int chunks, int* gx, int* gy) {
     const uint64_t per = N >= (uint64_t(1) << 17) ? 256 : 64;
-    *gx = int(std::min<uint64_t>((N + per - 1) / per, 256));
     *gy = std::max(1, std::min(chunks, 32));
+    *gx = int(std::min<uint64_t>((N + per - 1) / per, std::max(256, 2048 / *gy)));
 }
 
 size_t nz_counts(uint64_t N) { return size_t((N + kNzBlock - 1) / kNzBlock) + 1; }

@@ -3677,11 +3677,10 @@ extern "C" int vqe_expectation(const vqe_state* s, const vqe_hamiltonian* H, dou
     int gx, gy;
     expect_grid(N, hw->count, &gx, &gy);
     // the index list of the nonzero amplitudes, up to 64 MiB of it, where the
-    // outputs left out can pay for its three launches (8 us).  Reference state,
-    // listed / all outputs, us: two-body Hamiltonians on 4 qubits 36 / 28, 12 qubits
-    // 47 / 40, 14 qubits 50 / 46, 15 qubits 51 / 71, 16 qubits 52 / 129; 200 diagonal
-    // strings on 15 qubits 43 / 44, 16 qubits 43 / 60
-    bool listed = s->n <= 24 && double(N) * (double(H->c.size()) + 2000.0) > 1e8;
+    // outputs left out can pay for it: all outputs take about 1 ps per amplitude
+    // and (sub)group of H, the list 8 us of launches and 8 ps per amplitude
+    const double all_us = 1e-6 * double(N) * double(H->groups.size() + H->subs.size());
+    bool listed = s->n <= 24 && all_us > 6.0 * (8.0 + 8e-6 * double(N));
     if (listed)   // (1 MiB: the call's other buffers)
         if (int rc = scratch_room(s->st, 4 * (N + nz_counts(N)) + (size_t(1) << 20), &listed)) return rc;
     StateCall c;
@@ -3690,6 +3689,7 @@ extern "C" int vqe_expectation(const vqe_state* s, const vqe_hamiltonian* H, dou
     c.sd.cgroups = hw->cgroups;
     c.sd.csubs = hw->csubs;
     c.sd.nb = hw->count;
+    c.sd.G = int32_t(H->groups.size());
     c.sd.tabs = dh->tabs;
     HIPCHK(hipMemcpyAsync(c.sd_dev, &c.sd, sizeof(StateDesc), hipMemcpyHostToDevice, s->st));
     uint32_t* words = listed ? c.cv.take<uint32_t>(N + nz_counts(N)) : nullptr;

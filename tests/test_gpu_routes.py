@@ -38,6 +38,17 @@ def test_expectation_lists_nonzero_amplitudes(n, listed):
     assert got["k_hx_dense"] == 1 and got["k_nz_count"] == int(listed) and sum(got.values()) == (5 if listed else 2)
 
 
+@pytest.mark.parametrize("n,k", [(16, 1), (18, 20), (20, 3)])
+def test_few_strings_need_no_list(n, k):
+    rng = np.random.default_rng(n)
+    H = vq.Hamiltonian.from_paulis(n, rng.integers(0, 1 << n, k), np.zeros(k, np.uint32), rng.normal(size=k))
+    t = torch.zeros(1 << n, dtype=torch.complex128, device="cuda")
+    t[5] = 1.0
+    s = vq.State.wrap(t)
+    got = launches(lambda: s.expectation(H))
+    assert got["k_hx_dense"] == 1 and sum(got.values()) == 2
+
+
 def _rotations(n, gates, width, seed):
     """Strings on `width` qubits (0: one to four), one angle each."""
     rng = np.random.default_rng(seed)
