@@ -1601,12 +1601,38 @@ static int ci_upload(const vqe_hamiltonian* H, CiHam* c) {
     return VQE_OK;
 }
 
+// Matrix elements of H in the string space, as a part of what a general
+// two-body Hamiltonian has there.
+static double ci_density(const vqe_hamiltonian* H, const CiSpace& cs) {
+    const int na = __builtin_popcount(cs.sa[0]), nb = __builtin_popcount(cs.sb[0]);
+    const double sa = double(na) * (cs.oa - na), sb = double(nb) * (cs.ob - nb);
+    const double all = double(cs.NA) * double(cs.NB) *
+                       (1.0 + sa + sb + sa * sb + double(binom(na, 2)) * double(binom(cs.oa - na, 2)) +
+                        double(binom(nb, 2)) * double(binom(cs.ob - nb, 2)));
+    double have = 0.0;
+    for (const GroupDesc& g : H->groups) {   // rows that a flip leaves in the space
+        const int pa = __builtin_popcount(g.x & 0x55555555u), pb = __builtin_popcount(g.x & 0xAAAAAAAAu);
+        if ((pa | pb) & 1) continue;
+        have += double(binom(pa, pa / 2)) * double(binom(cs.oa - pa, na - pa / 2)) * double(binom(pb, pb / 2)) *
+                double(binom(cs.ob - pb, nb - pb / 2));
+    }
+    return have / all;
+}
+
+// The matrix form's products take the same time whatever H holds, walking takes
+// time for what is there.  A general two-body Hamiltonian walks 1.9 to 2.6 times
+// as long (24 qubits 690 us against 268), so that below a third walking is ahead:
+// energy and gradient on 24 qubits, us, walking / matrix form, one Z string 1497 /
+// 1651, Hubbard chain 1497 / 1647, one-body random 1545 / 1652; with two thirds of
+// the elements 1960 / 1887.
+constexpr double kMmMinDensity = 1.0 / 3.0;
+
 // Matrix form of H on a string space (k_hx_mm.hip), from the families ci_ham
 // sorted its groups into, or null when H has none: a group outside the
 // families (other flips, or tables over other orbitals), a sign mask that is
 // not a Jordan-Wigner chain between the flipped orbitals, or a coefficient
 // that differs with the direction of a hop (more than rounding of the largest
-// coefficient) leaves H to the walking kernel.  Every Hamiltonian of real
+// coefficient) leaves H to the walking kernel, and so does a sparse H.  Every Hamiltonian of real
 // two-body integrals with their 8-fold symmetry has one.
 static int ci_matrix(const vqe_hamiltonian* H, CiHam* c, const CiSpace& cs, const CiMatrix** out) {
     std::lock_guard<std::mutex> lk(H->mu);
@@ -1617,6 +1643,7 @@ static int ci_matrix(const vqe_hamiltonian* H, CiHam* c, const CiSpace& cs, cons
     }
     *out = c->mm[&cs] = nullptr;
     if (!cs.mm_ok || !c->diag.on || !c->psplit || !c->rgroups_h.empty() || !c->groups_h.empty()) return VQE_OK;
+    if (ci_density(H, cs) < kMmMinDensity) return VQE_OK;
     const int oa = cs.oa, ob = cs.ob, pa = oa * (oa - 1) / 2, n = H->n;
     const int Mp = cs.mm.m_pad, NAp = cs.mm.na_pad, NBp = cs.mm.nb_pad;
     double big = 0.0;   // of the flips (not the diagonal: a constant has no part in them)

@@ -143,3 +143,20 @@ def test_two_body_hamiltonians_have_the_matrix_form(n):
         H = vq.Hamiltonian.from_integrals(n, h0 + 1e3, 10.0 ** (seed - 1) * h, g)
         got = launches(lambda: vq.energy_grad(H, A, n // 2, np.array([0.1, -0.2])))
         assert got["k_hx_cross"] > 0 and got["k_hx_ci"] == 0
+
+
+@pytest.mark.parametrize("n", [16, 20, 24])
+@pytest.mark.parametrize("kind", ["z", "hubbard", "one-body"])
+def test_sparse_hamiltonians_are_walked(n, kind):
+    ns = (n + 1) // 2
+    chain, g = -(np.eye(ns, k=1) + np.eye(ns, k=-1)), np.zeros((ns,) * 4)
+    if kind == "hubbard":
+        for i in range(ns):
+            g[i, i, i, i] = 4.0
+    if kind == "z":
+        H = vq.Hamiltonian.from_paulis(n, [0], [1], [1.0])
+    else:
+        H = vq.Hamiltonian.from_integrals(n, 0.0, chain if kind == "hubbard" else random_integrals(n, 1)[1], g)
+    A = vq.Ansatz.uccsd(n, n // 2).select(np.arange(2, dtype=np.int32))
+    got = launches(lambda: vq.energy_grad(H, A, n // 2, np.array([0.1, -0.2])))
+    assert got["k_hx_cross"] == 0 and got["k_hx_ci"] == 1
