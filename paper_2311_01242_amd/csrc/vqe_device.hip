@@ -3069,7 +3069,13 @@ static int make_eval_plan(const vqe_ansatz* A, int ne, bool batched, EvalPlan* e
         // tiles is fastest with few blocks: 30 complex states of 18 qubits and 4
         // electrons L = 10 / 14 403 / 253 us)
         int product_L = 0;
-        if (force_L == 0 && binom((n + 1) / 2, (ne + 1) / 2) * binom(n / 2, ne / 2) > kWholeMax && tn.product_L > 0 && g_packed_enabled.load() >= 2 && (n + 1) / 2 <= kCiMaxBits &&
+        // Pool gradients (the callers without whole states) of fewer than 16 gates
+        // keep the tuning's: the sweep over the pool is then longer than the runs
+        // (20 qubits, 875 operators, 4 / 16 / 64 gates, L = 10 144 / 163 / 213 us, L = 12
+        // 134 / 164 / 246; 18 qubits L = 9 119 / 138 / 169, L = 12 115 / 137 / 187)
+        const bool long_runs = whole_ok || ep->M >= 16;
+        if (force_L == 0 && long_runs && binom((n + 1) / 2, (ne + 1) / 2) * binom(n / 2, ne / 2) > kWholeMax &&
+            tn.product_L > 0 && g_packed_enabled.load() >= 2 && (n + 1) / 2 <= kCiMaxBits &&
             binom(n / 2, ne / 2) <= kCiMaxCols)
             product_L = tn.product_L;
         const int need = g_packed_enabled.load() ? packed_min_L(A, ne) : -1;
